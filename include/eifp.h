@@ -142,7 +142,8 @@ eifp_status eifp_jump(eifp_solver *s, double tau, long long nsteps);
  * inverse), z-inverse (which also finalizes the invariants, in one extra workgroup),
  * x-inverse (complex-to-real; between two steps of the call one kernel does this
  * step's x-inverse and the next step's x-forward, and its time is counted here), and
- * the gap where a separate finalize would run (kept for layout; near zero).
+ * the gap where a separate finalize would run (kept for layout; near zero).  Grids that
+ * run the x and z transforms as one kernel have it in the x slots, the z slots near zero.
  * Synchronises the stream before returning.  Errors as eifp_step, plus INVALID_ARG for
  * NULL pass_ms. */
 eifp_status eifp_step_timed(eifp_solver *s, double tau, long long nsteps, double *pass_ms);

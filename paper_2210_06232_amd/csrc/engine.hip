@@ -48,6 +48,13 @@ bool use_plane(const Engine& en) {
     return plane_ok<T>(en.g) && en.g.M <= en.nrec;
 }
 
+// Grids whose (x, z) plane of one component fits in LDS run the z and x transforms
+// between two fused passes as one kernel.
+template <typename T>
+bool use_xz(const Engine& en) {
+    return xz_ok<T>(en.g);
+}
+
 }  // namespace
 
 template <typename T>
@@ -94,20 +101,25 @@ eifp_status run_passes(const Engine& en, int mode, const void* md, int nm, hipSt
         }
         return EIFP_OK;
     }
+    const bool xz = use_xz<T>(en);
     if (ev) EIFP_HIP_TRY(hipEventRecord(ev[0], st));
-    if ((rc = launch_x<T>(X_FWD, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x forward");
+    if ((rc = xz ? launch_xz<T>(X_FWD, en.g, md, nm, en.twx, en.twz, st) : launch_x<T>(X_FWD, en.g, md, nm, en.twx, st)))
+        return rc_to_status(rc, "x forward");
     if (ev) EIFP_HIP_TRY(hipEventRecord(ev[1], st));
-    if ((rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st))) return rc_to_status(rc, "z forward");
+    if (!xz && (rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st))) return rc_to_status(rc, "z forward");
     if (ev) EIFP_HIP_TRY(hipEventRecord(ev[2], st));
     if ((rc = launch_fused<T>(mode, AXIS_Y, en.g, md, nm, en.twy, want_inv ? 1 : 0, st)))
         return rc_to_status(rc, "fused y pass");
     if (ev) EIFP_HIP_TRY(hipEventRecord(ev[3], st));
     if (mode == Z_STEP) {
         // the z inverse also finalizes the invariant partials (one extra workgroup per member)
-        if ((rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, want_inv ? en.nparts : 0)))
+        const int fin = want_inv ? en.nparts : 0;
+        if (!xz && (rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, fin)))
             return rc_to_status(rc, "z inverse");
         if (ev) EIFP_HIP_TRY(hipEventRecord(ev[4], st));
-        if ((rc = launch_x<T>(X_INV, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x inverse");
+        if ((rc = xz ? launch_xz<T>(X_INV, en.g, md, nm, en.twx, en.twz, st, fin)
+                     : launch_x<T>(X_INV, en.g, md, nm, en.twx, st)))
+            return rc_to_status(rc, "x inverse");
         if (ev) EIFP_HIP_TRY(hipEventRecord(ev[5], st));
     } else if (ev) {
         EIFP_HIP_TRY(hipEventRecord(ev[4], st));
@@ -130,13 +142,15 @@ template <typename T>
 eifp_status run_steps(const Engine& en, const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev,
                       long long inv_from, bool combine_x) {
     int rc;
-    const bool plane = use_plane<T>(en);
+    const bool plane = use_plane<T>(en), xz = !plane && use_xz<T>(en);
     for (long long n = 0; n < nsteps; ++n) {
         const bool want_inv = n >= inv_from;
         hipEvent_t* e = ev ? ev + 7 * n : nullptr;
         const bool first = n == 0 || !combine_x, last = n + 1 == nsteps || !combine_x;
         if (e) EIFP_HIP_TRY(hipEventRecord(e[0], st));
-        if (first && (rc = launch_x<T>(X_FWD, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x forward");
+        if (first && (rc = xz ? launch_xz<T>(X_FWD, en.g, md, nm, en.twx, en.twz, st)
+                              : launch_x<T>(X_FWD, en.g, md, nm, en.twx, st)))
+            return rc_to_status(rc, "x forward");
         if (e) EIFP_HIP_TRY(hipEventRecord(e[1], st));
         if (plane) {
             eifp_status s = run_plane_middle<T>(en, md, nm, st, e, want_inv);
@@ -149,16 +163,18 @@ eifp_status run_steps(const Engine& en, const void* md, int nm, long long nsteps
             }
             continue;
         }
-        if ((rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st, 0, first ? 1 : 0)))
+        if (!xz && (rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st, 0, first ? 1 : 0)))
             return rc_to_status(rc, "z forward");
         if (e) EIFP_HIP_TRY(hipEventRecord(e[2], st));
         if ((rc = launch_fused<T>(Z_STEP, AXIS_Y, en.g, md, nm, en.twy, want_inv ? 1 : 0, st)))
             return rc_to_status(rc, "fused y pass");
         if (e) EIFP_HIP_TRY(hipEventRecord(e[3], st));
-        if ((rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, want_inv ? en.nparts : 0)))
+        const int fin = want_inv ? en.nparts : 0;
+        if (!xz && (rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, fin)))
             return rc_to_status(rc, "z inverse");
         if (e) EIFP_HIP_TRY(hipEventRecord(e[4], st));
-        if ((rc = launch_x<T>(last ? X_INV : X_INVFWD, en.g, md, nm, en.twx, st)))
+        if ((rc = xz ? launch_xz<T>(last ? X_INV : X_INVFWD, en.g, md, nm, en.twx, en.twz, st, fin)
+                     : launch_x<T>(last ? X_INV : X_INVFWD, en.g, md, nm, en.twx, st)))
             return rc_to_status(rc, "x inverse");
         if (e) {
             EIFP_HIP_TRY(hipEventRecord(e[5], st));
@@ -171,8 +187,12 @@ eifp_status run_steps(const Engine& en, const void* md, int nm, long long nsteps
 template <typename T>
 eifp_status run_spectrum(const Engine& en, const void* md, int nm, hipStream_t st) {
     int rc;
-    if ((rc = launch_x<T>(X_FWD, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x forward");
-    if ((rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st))) return rc_to_status(rc, "z forward");
+    if (use_xz<T>(en)) {
+        if ((rc = launch_xz<T>(X_FWD, en.g, md, nm, en.twx, en.twz, st))) return rc_to_status(rc, "x and z forward");
+    } else {
+        if ((rc = launch_x<T>(X_FWD, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x forward");
+        if ((rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st))) return rc_to_status(rc, "z forward");
+    }
     if ((rc = launch_c2c<T>(false, AXIS_Y, en.g, md, nm, en.twy, st))) return rc_to_status(rc, "y forward");
     return EIFP_OK;
 }
@@ -182,8 +202,13 @@ eifp_status run_jump(const Engine& en, const void* md, int nm, hipStream_t st, b
     int rc;
     if ((rc = launch_fused<T>(Z_JUMP, AXIS_Y, en.g, md, nm, en.twy, want_inv ? 1 : 0, st)))
         return rc_to_status(rc, "fused jump pass");
-    if ((rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, want_inv ? en.nparts : 0)))
-        return rc_to_status(rc, "z inverse");
+    const int fin = want_inv ? en.nparts : 0;
+    if (use_xz<T>(en)) {
+        if ((rc = launch_xz<T>(X_INV, en.g, md, nm, en.twx, en.twz, st, fin)))
+            return rc_to_status(rc, "z and x inverse");
+        return EIFP_OK;
+    }
+    if ((rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, fin))) return rc_to_status(rc, "z inverse");
     if ((rc = launch_x<T>(X_INV, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x inverse");
     return EIFP_OK;
 }

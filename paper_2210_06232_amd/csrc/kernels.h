@@ -133,11 +133,10 @@ __device__ __forceinline__ void store_row(cpx<T>* out, const cpx<T> (&v)[P::E], 
 // Row helpers.  x_forward_row: v holds the row's M complex values (pairs of reals) at
 // positions t + T m_first(i); length-M FFT, then the split
 //   X[k] = (Z[k] + conj Z[M-k])/2 - (i/2) W^k (Z[k] - conj Z[M-k]),  W = exp(-2 pi i/Nx),
-// stored to out (X[0] + i X[M] in slot 0).  The row's LDS and the twiddle table are
-// ordered by the caller (the table staged behind a block barrier).
-template <typename T, class P, int LD>
-__device__ __forceinline__ void x_forward_row(cpx<T> (&v)[P::E], int t, LdsRows<T, LD>& lds, const cpx<T>* s_tw,
-                                              cpx<T>* out, bool active) {
+// left in v at positions t + T m_last(i) (X[0] + i X[M] in slot 0).  The row's LDS and the
+// twiddle table are ordered by the caller (the table staged behind a block barrier).
+template <typename T, class P, class Lds>
+__device__ __forceinline__ void x_forward_row(cpx<T> (&v)[P::E], int t, Lds& lds, const cpx<T>* s_tw) {
     constexpr int M = P::N, E = P::E, TT = P::T;
     static_assert(64 % TT == 0, "a row within one wave");
     fft_pencil<P, false, 2>(v, t, lds, s_tw);
@@ -158,20 +157,21 @@ __device__ __forceinline__ void x_forward_row(cpx<T> (&v)[P::E], int t, LdsRows<
             v[i] = ev + twmul<false>(s_tw, k, 2 * M, od);
         }
     }
-    store_row<T, P, true>(out, v, t, active);
 }
 
 // x_inverse_row: v holds the packed half spectrum of a row at positions t + T m_first(i);
 // merge Z[k] = (X[k] + conj X[M-k]) + i W^-k (X[k] - conj X[M-k]) (Z[0] from X[0], X[M]),
 // then the inverse length-M FFT: v ends at positions t + T m_last(i) (the row's reals in
-// pairs, unscaled).
-template <typename T, class P, int LD>
-__device__ __forceinline__ void x_inverse_row(cpx<T> (&v)[P::E], int t, LdsRows<T, LD>& lds, const cpx<T>* s_tw) {
+// pairs, unscaled).  STAGED: the row's LDS already holds the half spectrum.
+template <typename T, class P, bool STAGED = false, class Lds>
+__device__ __forceinline__ void x_inverse_row(cpx<T> (&v)[P::E], int t, Lds& lds, const cpx<T>* s_tw) {
     constexpr int M = P::N, E = P::E, TT = P::T;
     static_assert(64 % TT == 0, "a row within one wave");
+    if constexpr (!STAGED) {
 #pragma unroll
-    for (int i = 0; i < E; ++i) lds.st(t + TT * m_first<P>(i), v[i]);
-    lds.sync();
+        for (int i = 0; i < E; ++i) lds.st(t + TT * m_first<P>(i), v[i]);
+        lds.sync();
+    }
 #pragma unroll
     for (int i = 0; i < E; ++i) {
         const int k = t + TT * m_first<P>(i);
@@ -208,7 +208,8 @@ k_x_fwd(const MemberDesc<T>* __restrict__ md, long nrows, const cpx<T>* __restri
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = in[t + TT * m_first<P>(i)];
     LdsRows<T, LD> lds{s_re, s_im, p};
-    x_forward_row<T, P, LD>(v, t, lds, s_tw, dst + row * M, active);
+    x_forward_row<T, P>(v, t, lds, s_tw);
+    store_row<T, P, true>(dst + row * M, v, t, active);
 }
 
 // Rows in descending order (EIFP_MALL_ORDER): the z inverse pass wrote the last
@@ -238,7 +239,7 @@ __device__ __forceinline__ void x_inv_body(const MemberDesc<T>* __restrict__ md,
     cpx<T> v[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = in[t + TT * m_first<P>(i)];
-    x_inverse_row<T, P, LD>(v, t, lds, s_tw);
+    x_inverse_row<T, P>(v, t, lds, s_tw);
     store_row<T, P, true>(dst + row * M, v, t, active);
 }
 template <typename T, class P, int NP>
@@ -276,7 +277,7 @@ __device__ __forceinline__ void x_invfwd_body(const MemberDesc<T>* __restrict__ 
     cpx<T> v[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = in[t + TT * m_first<P>(i)];
-    x_inverse_row<T, P, LD>(v, t, lds, s_tw);
+    x_inverse_row<T, P>(v, t, lds, s_tw);
     // the physical row as materialised values of T, as a store and a reload would give
     // them: the empty asm keeps the compiler from merging the inverse's last operations
     // with the forward's first ones (without it, FP64 rows differ in the last bit from
@@ -284,7 +285,8 @@ __device__ __forceinline__ void x_invfwd_body(const MemberDesc<T>* __restrict__ 
 #pragma unroll
     for (int i = 0; i < E; ++i) asm volatile("" : "+v"(v[i].x), "+v"(v[i].y));
     last_to_first<P>(v);
-    x_forward_row<T, P, LD>(v, t, lds, s_tw, work + row * M, active);
+    x_forward_row<T, P>(v, t, lds, s_tw);
+    store_row<T, P, true>(work + row * M, v, t, active);
 }
 template <typename T, class P, int NP>
 __global__ void __launch_bounds__(P::T * NP)

@@ -6,7 +6,8 @@
 // fused y (forward, propagator, invariant partials, inverse; all six components),
 // z inverse (with the invariant finalize), x inverse (C2R merge); between two steps the
 // x inverse and the next x forward run as one kernel.  Grids whose (y, z) plane fits in
-// LDS run the three middle passes as one plane pass.  The fused pass runs along y
+// LDS run the three middle passes as one plane pass; grids whose (x, z) plane of one
+// component fits run the x and z transforms between two fused passes as one.  The fused pass runs along y
 // because its pencils are then M complex elements apart, while the strided z axis is
 // handled by the single-component pass, which can use wide tiles.
 //
@@ -46,6 +47,17 @@ bool plane_ok(const Grid3& g);
 template <typename T>
 int launch_plane(const Grid3& g, const void* md, int nm, const void* twy, const void* twz, int want_inv,
                  hipStream_t st);
+
+// The x and z transforms between two fused passes as one kernel per (x, z) plane, where
+// it is compiled and the faster path (xz_ok; kUnsupported from launch_xz otherwise):
+// X_FWD (x forward, z forward: state -> work), X_INV (z inverse, x inverse: work ->
+// state) or X_INVFWD (between two steps: all four, in place on work).  Every kind may
+// run with work == state.  fin_nparts as in launch_c2c (X_INV and X_INVFWD).
+template <typename T>
+bool xz_ok(const Grid3& g);
+template <typename T>
+int launch_xz(int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz, hipStream_t st,
+              int fin_nparts = 0);
 
 // single-component C2C along y or z on each member's work buffer (six components, in
 // place); fin_nparts > 0 also finalizes each member's invariant partials (that many

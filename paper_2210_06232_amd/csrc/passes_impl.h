@@ -3,6 +3,7 @@
 #pragma once
 #include "passes.h"
 #include "small_plane.h"
+#include "xz_plane.h"
 
 namespace eifp {
 
@@ -208,6 +209,23 @@ int run_c2c(bool inv, int axis, const Grid3& g, const void* md, int nm, const vo
 // finalize agree on it.
 // The fused pass's configuration for length N: the split form (k_fused_split) or the
 // six-components-per-thread form (k_fused), its tile width, threads and persistence.
+// Fused workgroups share a member's tiles: as many as the device holds at once for a
+// persistent form, one per tile otherwise.
+inline int share_tiles(int ntiles, int resident) {
+    if (resident <= 0 || resident >= ntiles) return ntiles;
+    return resident >= 8 ? resident & ~7 : resident;
+}
+// CUs times the kernel's resident workgroups per CU (0 without a device)
+inline int resident_workgroups(const void* kernel, int threads) {
+    int dev = 0, cus = 0, nb = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, threads, 0) != hipSuccess || cus <= 0 || nb <= 0) {
+        (void)hipGetLastError();  // leave no error behind for the next launch check
+        return 0;
+    }
+    return cus * nb;
+}
 template <typename T, int N, int AXIS> struct FusedSel {
     static constexpr bool split = ZCfgS<T, N>::ok;
     static constexpr int B = split ? ZCfgS<T, N>::B : ZCfg<T, N>::B;
@@ -227,19 +245,8 @@ int fused_workgroups(const Grid3& g) {
     using S = FusedSel<T, N, AXIS>;
     const int ntiles = ((g.M + S::B - 1) / S::B) * axis_geom(AXIS, g).n_outer;
     if (!S::persist) return ntiles;
-    static const int resident = [] {
-        int dev = 0, cus = 0, nb = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, S::step_kernel(), S::threads, 0) != hipSuccess ||
-            cus <= 0 || nb <= 0) {
-            (void)hipGetLastError();  // leave no error behind for the next launch check
-            return 0;
-        }
-        return cus * nb;
-    }();
-    if (resident <= 0 || resident >= ntiles) return ntiles;
-    return resident >= 8 ? resident & ~7 : resident;
+    static const int resident = resident_workgroups(S::step_kernel(), S::threads);
+    return share_tiles(ntiles, resident);
 }
 
 template <typename T, int N, int MODE, int AXIS>
@@ -414,6 +421,94 @@ int launch_plane(const Grid3& g, const void* md, int nm, const void* twy, const 
     }
 }
 
+// (x, z) plane pass: pairs of half length M and z length N whose plane fits in LDS; in
+// FP32, where the work is issue-bound, only while two workgroups share a CU (us per step,
+// separate passes / plane pass, Ny = 64: 192x64x64 FP32 68.0 / 52.8, 128x64x192 84.5 /
+// 86.7, 64x64x512 109 / 121; FP64 192x64x96 131 / 115, 128x64x128 99 / 71).
+template <typename T, int M, int N> struct XzPair {
+    static constexpr bool ok() {
+        if constexpr (M < 8 || N < 8 || M * N > 10240) {
+            return false;
+        } else {
+            using C = XzCfg<T, Plan<N, XYE<N>::E>, Plan<M, XYE<M>::E>>;
+            return C::lds_bytes <= (sizeof(T) == 4 ? C::HALF : C::FULL);
+        }
+    }
+};
+template <typename T, int M, int N>
+int run_xz(int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz, hipStream_t st,
+           int fin_nparts) {
+    using PZ = Plan<N, XYE<N>::E>;
+    using PX = Plan<M, XYE<M>::E>;
+    using C = XzCfg<T, PZ, PX>;
+    const int nplanes = 6 * g.ny;
+    int nwg = nplanes;
+    if (C::PERSIST) {
+        static const int resident = resident_workgroups((const void*)k_xz<T, PZ, PX, X_INVFWD>, C::NT);
+        if (resident > 0 && resident < nplanes) nwg = resident;
+    }
+    const dim3 grid((unsigned)nwg + (!C::PERSIST && fin_nparts > 0 ? 1u : 0u), 1u, (unsigned)nm);
+    const dim3 block(C::NT);
+    const MemberDesc<T>* d = (const MemberDesc<T>*)md;
+    if (kind == X_FWD)
+        hipLaunchKernelGGL((k_xz<T, PZ, PX, X_FWD>), grid, block, 0, st, d, g.ny, g.cs(), (const cpx<T>*)twz,
+                           (const cpx<T>*)twx, fin_nparts);
+    else if (kind == X_INV)
+        hipLaunchKernelGGL((k_xz<T, PZ, PX, X_INV>), grid, block, 0, st, d, g.ny, g.cs(), (const cpx<T>*)twz,
+                           (const cpx<T>*)twx, fin_nparts);
+    else
+        hipLaunchKernelGGL((k_xz<T, PZ, PX, X_INVFWD>), grid, block, 0, st, d, g.ny, g.cs(), (const cpx<T>*)twz,
+                           (const cpx<T>*)twx, fin_nparts);
+    return check_launch();
+}
+// launch: false only reports whether the pair is compiled (kOk or kUnsupported)
+template <typename T, int M>
+int xz_pair(bool launch, int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz,
+            hipStream_t st, int fin_nparts) {
+    switch (g.nz) {
+#define EIFP_CASE(N)                                                                               \
+    case N:                                                                                        \
+        if constexpr (XzPair<T, M, N>::ok())                                                       \
+            return launch ? run_xz<T, M, N>(kind, g, md, nm, twx, twz, st, fin_nparts) : (int)kOk; \
+        return kUnsupported;
+        EIFP_AXIS_SIZES(EIFP_CASE)
+#undef EIFP_CASE
+        default:
+            return kUnsupported;
+    }
+}
+// The pairs are instantiated by half length in translation units of their own
+// (passes_xz_*.hip), so that they compile in parallel.
+#define EIFP_XZ_HALF(T, M) \
+    template int xz_pair<T, M>(bool, int, const Grid3&, const void*, int, const void*, const void*, hipStream_t, int);
+#define EIFP_CASE(M)              \
+    extern EIFP_XZ_HALF(double, M) \
+    extern EIFP_XZ_HALF(float, M)
+EIFP_HALF_SIZES(EIFP_CASE)
+#undef EIFP_CASE
+template <typename T>
+int xz_dispatch(bool launch, int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz,
+                hipStream_t st, int fin_nparts) {
+    switch (g.M) {
+#define EIFP_CASE(MM) \
+    case MM:          \
+        return xz_pair<T, MM>(launch, kind, g, md, nm, twx, twz, st, fin_nparts);
+        EIFP_HALF_SIZES(EIFP_CASE)
+#undef EIFP_CASE
+        default:
+            return kUnsupported;
+    }
+}
+template <typename T>
+bool xz_ok(const Grid3& g) {
+    return xz_dispatch<T>(false, 0, g, nullptr, 1, nullptr, nullptr, nullptr, 0) == kOk;
+}
+template <typename T>
+int launch_xz(int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz, hipStream_t st,
+              int fin_nparts) {
+    return xz_dispatch<T>(true, kind, g, md, nm, twx, twz, st, fin_nparts);
+}
+
 template <typename T>
 int launch_finalize(const void* md, int nm, int nparts, hipStream_t st, bool extended) {
     if (extended)
@@ -431,6 +526,8 @@ int launch_finalize(const void* md, int nm, int nparts, hipStream_t st, bool ext
 #define EIFP_INSTANTIATE(T)                                                                                   \
     template int launch_x<T>(int, const Grid3&, const void*, int, const void*, hipStream_t, int);             \
     template bool plane_ok<T>(const Grid3&);                                                                 \
+    template bool xz_ok<T>(const Grid3&);                                                                     \
+    template int launch_xz<T>(int, const Grid3&, const void*, int, const void*, const void*, hipStream_t, int); \
     template int launch_plane<T>(const Grid3&, const void*, int, const void*, const void*, int, hipStream_t); \
     template int launch_fused<T>(int, int, const Grid3&, const void*, int, const void*, int, hipStream_t);    \
     template int fused_partial_count<T>(int, const Grid3&);                                                   \

@@ -1,0 +1,10 @@
+// FP32 instances of the (x, z) plane pass (k_xz) for half lengths M = 64 to 256.
+#include "passes_impl.h"
+
+namespace eifp {
+EIFP_XZ_HALF(float, 64)
+EIFP_XZ_HALF(float, 96)
+EIFP_XZ_HALF(float, 128)
+EIFP_XZ_HALF(float, 192)
+EIFP_XZ_HALF(float, 256)
+}
