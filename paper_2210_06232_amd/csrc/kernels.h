@@ -608,9 +608,6 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[Q], double* __r
 // Horner in r^2 through the terms of degree 17 and 16 (the first terms left out are below
 // 1e-19 and 3e-18 at |r| = 1/4), then the n mod 4 quarter turns.  About half the
 // instructions of the library's sincospi, within a couple of units in the last place.
-#ifndef EIFP_SERIES_SINCOS
-#define EIFP_SERIES_SINCOS 1
-#endif
 __host__ __device__ inline void sincospi_series(double x, double* sn, double* cs) {
     const double n = rint(2.0 * x);
     const double r = fma(-0.5, n, x);
@@ -649,75 +646,90 @@ __host__ __device__ inline void sincospi_series(double x, double* sn, double* cs
 // which is the c/s matrix of Prop. 2.2 applied as in Alg. 2 step 4 (c = k k^T +
 // cos(theta) (I - k k^T), s_12 = i sin(theta) k_z, ...).  |b| = 0 keeps the mode.
 // All coefficients are formed in FP64 and rounded to T; everything is scaled by 1/N_S.
-#ifndef EIFP_PROP_COMP
-#define EIFP_PROP_COMP 1
-#endif
 template <typename T>
-__device__ __forceinline__ void propagate_mode(cpx<T>* h, cpx<T>* e, double bx, double by, double bz, const PropParams& pp) {
+struct PropCoef {
+    T kx, ky, kz, cT, dL, sE, sH;
+};
+template <>
+struct PropCoef<float> {
+    float kh[3], kl[3], cTh, cTl, sEh, sEl, sHh, sHl, dL;
+};
+template <typename T>
+__device__ __forceinline__ PropCoef<T> prop_coef(double bx, double by, double bz, const PropParams& pp) {
     // |b| = 0 needs no branch: theta = 0 gives cos = 1, sin = 0 and the k terms drop out
     const double b2 = bx * bx + by * by + bz * bz;
     const double ib = b2 > 0.0 ? rsqrt(b2) : 0.0;  // 1/|b| (0 for the zero mode)
     const double bn = b2 * ib;                      // |b|
     // the phase in half-turns, theta / pi, so that the reduction is exact for any tau
     double sn, cs;
-    if (EIFP_SERIES_SINCOS) sincospi_series(pp.tau_s_over_pi * bn, &sn, &cs);
-    else sincospi(pp.tau_s_over_pi * bn, &sn, &cs);
-    if constexpr (sizeof(T) == 4 && EIFP_PROP_COMP) {
+    sincospi_series(pp.tau_s_over_pi * bn, &sn, &cs);
+    PropCoef<T> p;
+    if constexpr (sizeof(T) == 4) {
         // FP32: every coefficient of the transverse rotation (cos, sin, the unit wave
         // vector in the cross products) enters as a rounded part plus its remainder,
         // folded into the FMA chain before the final rounding, so the per-mode rotation
         // is not biased in modulus from step to step
         const double kd[3] = {bx * ib, by * ib, bz * ib};
-        float kh_[3], kl_[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            kh_[c] = (float)kd[c];
-            kl_[c] = (float)(kd[c] - (double)kh_[c]);
+            p.kh[c] = (float)kd[c];
+            p.kl[c] = (float)(kd[c] - (double)p.kh[c]);
         }
         const double cTd = cs * pp.inv_ns, sEd = sn * pp.re * pp.inv_ns, sHd = sn * pp.rh * pp.inv_ns;
-        const float cTh = (float)cTd, cTl = (float)(cTd - (double)cTh);
-        const float sEh = (float)sEd, sEl = (float)(sEd - (double)sEh);
-        const float sHh = (float)sHd, sHl = (float)(sHd - (double)sHh);
-        const float dL = (float)((1.0 - cs) * pp.inv_ns);
-        const cpx<float> kh = {kh_[0] * (float)h[0].x + kh_[1] * (float)h[1].x + kh_[2] * (float)h[2].x,
-                               kh_[0] * (float)h[0].y + kh_[1] * (float)h[1].y + kh_[2] * (float)h[2].y};
-        const cpx<float> ke = {kh_[0] * (float)e[0].x + kh_[1] * (float)e[1].x + kh_[2] * (float)e[2].x,
-                               kh_[0] * (float)e[0].y + kh_[1] * (float)e[1].y + kh_[2] * (float)e[2].y};
-        // (k x U)_c = k_a U_b - k_b U_a with (a, b) = (y, z), (z, x), (x, y)
-        auto cross = [&](const float* ur, int c) {
-            const int a = (c + 1) % 3, b = (c + 2) % 3;
-            return __builtin_fmaf(kh_[a], ur[b],
-                                  __builtin_fmaf(-kh_[b], ur[a], __builtin_fmaf(kl_[a], ur[b], -(kl_[b] * ur[a]))));
-        };
-        const float her[3] = {(float)h[0].x, (float)h[1].x, (float)h[2].x}, hei[3] = {(float)h[0].y, (float)h[1].y, (float)h[2].y};
-        const float eer[3] = {(float)e[0].x, (float)e[1].x, (float)e[2].x}, eei[3] = {(float)e[0].y, (float)e[1].y, (float)e[2].y};
-        float xer[3], xei[3], xhr[3], xhi[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            xer[c] = cross(eer, c);
-            xei[c] = cross(eei, c);
-            xhr[c] = cross(her, c);
-            xhi[c] = cross(hei, c);
-        }
-        // H' = cT H + dL k (k.H) - sE i (k x E);  E' = cT E + dL k (k.E) + sH i (k x H);  i (a + ib) = -b + ia
-        auto comb = [&](float u, float x, float lon, float sh, float sl) {
-            return __builtin_fmaf(cTh, u, __builtin_fmaf(sh, x, __builtin_fmaf(cTl, u, __builtin_fmaf(sl, x, lon))));
-        };
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const float dk = dL * kh_[c];
-            const cpx<float> hn = {comb(her[c], xei[c], dk * kh.x, sEh, sEl), comb(hei[c], -xer[c], dk * kh.y, sEh, sEl)};
-            const cpx<float> en = {comb(eer[c], -xhi[c], dk * ke.x, sHh, sHl), comb(eei[c], xhr[c], dk * ke.y, sHh, sHl)};
-            h[c] = {(T)hn.x, (T)hn.y};
-            e[c] = {(T)en.x, (T)en.y};
-        }
-        return;
+        p.cTh = (float)cTd, p.cTl = (float)(cTd - (double)p.cTh);
+        p.sEh = (float)sEd, p.sEl = (float)(sEd - (double)p.sEh);
+        p.sHh = (float)sHd, p.sHl = (float)(sHd - (double)p.sHh);
+        p.dL = (float)((1.0 - cs) * pp.inv_ns);
+    } else {
+        p.kx = bx * ib, p.ky = by * ib, p.kz = bz * ib;
+        p.cT = cs * pp.inv_ns;          // transverse part
+        p.dL = (1.0 - cs) * pp.inv_ns;  // longitudinal minus transverse
+        p.sE = sn * pp.re * pp.inv_ns;
+        p.sH = sn * pp.rh * pp.inv_ns;
     }
-    const T kx = (T)(bx * ib), ky = (T)(by * ib), kz = (T)(bz * ib);
-    const T cT = (T)(cs * pp.inv_ns);                 // transverse part
-    const T dL = (T)((1.0 - cs) * pp.inv_ns);         // longitudinal minus transverse
-    const T sE = (T)(sn * pp.re * pp.inv_ns);
-    const T sH = (T)(sn * pp.rh * pp.inv_ns);
+    return p;
+}
+// The coefficients of the mirror mode (b_x, -b_y, b_z): |b| and so the phase are the same.
+__device__ __forceinline__ void mirror_y(PropCoef<double>& p) { p.ky = -p.ky; }
+__device__ __forceinline__ void mirror_y(PropCoef<float>& p) {
+    p.kh[1] = -p.kh[1];
+    p.kl[1] = -p.kl[1];
+}
+__device__ __forceinline__ void prop_apply(cpx<float>* h, cpx<float>* e, const PropCoef<float>& p) {
+    const cpx<float> kh = {p.kh[0] * h[0].x + p.kh[1] * h[1].x + p.kh[2] * h[2].x,
+                           p.kh[0] * h[0].y + p.kh[1] * h[1].y + p.kh[2] * h[2].y};
+    const cpx<float> ke = {p.kh[0] * e[0].x + p.kh[1] * e[1].x + p.kh[2] * e[2].x,
+                           p.kh[0] * e[0].y + p.kh[1] * e[1].y + p.kh[2] * e[2].y};
+    // (k x U)_c = k_a U_b - k_b U_a with (a, b) = (y, z), (z, x), (x, y)
+    auto cross = [&](const float* ur, int c) {
+        const int a = (c + 1) % 3, b = (c + 2) % 3;
+        return __builtin_fmaf(p.kh[a], ur[b],
+                              __builtin_fmaf(-p.kh[b], ur[a], __builtin_fmaf(p.kl[a], ur[b], -(p.kl[b] * ur[a]))));
+    };
+    const float her[3] = {h[0].x, h[1].x, h[2].x}, hei[3] = {h[0].y, h[1].y, h[2].y};
+    const float eer[3] = {e[0].x, e[1].x, e[2].x}, eei[3] = {e[0].y, e[1].y, e[2].y};
+    float xer[3], xei[3], xhr[3], xhi[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        xer[c] = cross(eer, c);
+        xei[c] = cross(eei, c);
+        xhr[c] = cross(her, c);
+        xhi[c] = cross(hei, c);
+    }
+    // H' = cT H + dL k (k.H) - sE i (k x E);  E' = cT E + dL k (k.E) + sH i (k x H);  i (a + ib) = -b + ia
+    auto comb = [&](float u, float x, float lon, float sh, float sl) {
+        return __builtin_fmaf(p.cTh, u, __builtin_fmaf(sh, x, __builtin_fmaf(p.cTl, u, __builtin_fmaf(sl, x, lon))));
+    };
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float dk = p.dL * p.kh[c];
+        h[c] = {comb(her[c], xei[c], dk * kh.x, p.sEh, p.sEl), comb(hei[c], -xer[c], dk * kh.y, p.sEh, p.sEl)};
+        e[c] = {comb(eer[c], -xhi[c], dk * ke.x, p.sHh, p.sHl), comb(eei[c], xhr[c], dk * ke.y, p.sHh, p.sHl)};
+    }
+}
+__device__ __forceinline__ void prop_apply(cpx<double>* h, cpx<double>* e, const PropCoef<double>& p) {
+    using T = double;
+    const T kx = p.kx, ky = p.ky, kz = p.kz, cT = p.cT, dL = p.dL, sE = p.sE, sH = p.sH;
     const cpx<T> kh = {kx * h[0].x + ky * h[1].x + kz * h[2].x, kx * h[0].y + ky * h[1].y + kz * h[2].y};
     const cpx<T> ke = {kx * e[0].x + ky * e[1].x + kz * e[2].x, kx * e[0].y + ky * e[1].y + kz * e[2].y};
     // k x U
@@ -736,6 +748,10 @@ __device__ __forceinline__ void propagate_mode(cpx<T>* h, cpx<T>* e, double bx, 
         h[c] = hn;
         e[c] = en;
     }
+}
+template <typename T>
+__device__ __forceinline__ void propagate_mode(cpx<T>* h, cpx<T>* e, double bx, double by, double bz, const PropParams& pp) {
+    prop_apply(h, e, prop_coef<T>(bx, by, bz, pp));
 }
 
 // Per-thread sums of the basic invariants along one y pencil.  The thread's column (so

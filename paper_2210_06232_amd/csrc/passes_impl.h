@@ -4,6 +4,7 @@
 #include "passes.h"
 #include "small_plane.h"
 #include "xz_plane.h"
+#include "fused_wide.h"
 
 namespace eifp {
 
@@ -209,6 +210,32 @@ int run_c2c(bool inv, int axis, const Grid3& g, const void* md, int nm, const vo
 // finalize agree on it.
 // The fused pass's configuration for length N: the split form (k_fused_split) or the
 // six-components-per-thread form (k_fused), its tile width, threads and persistence.
+// The one-component-per-wave form (k_fused_wide): values per thread, and where it is used.
+// 8 or 12 values up to length 64 (more waves for the few tiles of small grids), 16 or 12
+// above (one exchange less per transform at 128 and 256).
+template <typename T, int N> struct WideSel {
+    static constexpr int E = N % 3 == 0 ? (N >= 12 ? 12 : 6) : N == 16 ? 4 : N <= 8 ? N : N <= 64 ? 8 : 16;
+    using P = Plan<N, E>;
+    using C = WideCfg<T, P>;
+    // The largest number of tiles a member may have for this form: -1 none (the length is
+    // not compiled), 0 no limit.  With few tiles the form's six waves a tile fill the
+    // device where the other forms' one to four cannot; with many the other forms' wider
+    // tiles and fewer LDS passes win, except in FP64 at 64 to 192, where its lower
+    // register need (one component instead of six or three a thread) does.  Fused pass,
+    // us, other form / this one, FP64: 64^3 (256 tiles) 23.9 / 14.1, 64x32x256 (512) 23.7 /
+    // 18.9, 256x32x256 (2048) 48.4 / 52.3, 256x64x256 (4096) 102 / 95, 128^3 55.2 / 43.5,
+    // 192^3 248 / 179, 64x256x256 (2048) 104 / 100, 256^3 (16384) 418 / 480; FP32: 64^3
+    // 19.0 / 12.4, 96^3 (576) 30.3 / 28.1, 64x192x64 (512) 29.1 / 24.7, 64x64x256 (1024) 27.8
+    // / 31.1, 256^3 243 / 433.
+    static constexpr int max_tiles = N < 8 || N > 256 || C::lds_bytes > 160 * 1024 ? -1
+                                     : sizeof(T) == 4                               ? 640
+                                     : N >= 64 && N <= 192                          ? 0
+                                     : N == 256                                     ? 2048
+                                                                                    : 512;
+    static constexpr bool compiled = max_tiles >= 0, always = max_tiles == 0;
+    static int tiles(const Grid3& g, int n_outer) { return ((g.M + C::B - 1) / C::B) * n_outer; }
+    static bool use(const Grid3& g, int n_outer) { return compiled && (always || tiles(g, n_outer) <= max_tiles); }
+};
 // Fused workgroups share a member's tiles: as many as the device holds at once for a
 // persistent form, one per tile otherwise.
 inline int share_tiles(int ntiles, int resident) {
@@ -242,32 +269,53 @@ template <typename T, int N, int AXIS> struct FusedSel {
 
 template <typename T, int N, int AXIS>
 int fused_workgroups(const Grid3& g) {
-    using S = FusedSel<T, N, AXIS>;
-    const int ntiles = ((g.M + S::B - 1) / S::B) * axis_geom(AXIS, g).n_outer;
-    if (!S::persist) return ntiles;
-    static const int resident = resident_workgroups(S::step_kernel(), S::threads);
-    return share_tiles(ntiles, resident);
+    const int n_outer = axis_geom(AXIS, g).n_outer;
+    if constexpr (WideSel<T, N>::compiled) {
+        using W = WideSel<T, N>;
+        if (W::use(g, n_outer)) {
+            const int ntiles = W::tiles(g, n_outer);
+            if (!W::C::PERSIST) return ntiles;
+            static const int resident = resident_workgroups((const void*)k_fused_wide<T, typename W::P, Z_STEP>, W::C::NT);
+            return share_tiles(ntiles, resident);
+        }
+    }
+    if constexpr (!WideSel<T, N>::always) {
+        using S = FusedSel<T, N, AXIS>;
+        const int ntiles = ((g.M + S::B - 1) / S::B) * n_outer;
+        if (!S::persist) return ntiles;
+        static const int resident = resident_workgroups(S::step_kernel(), S::threads);
+        return share_tiles(ntiles, resident);
+    }
+    return -1;
 }
 
 template <typename T, int N, int MODE, int AXIS>
 void run_fused_k(const Grid3& g, const void* md, int nm, const void* tw, int want_inv, hipStream_t st) {
     const AxisGeom a = axis_geom(AXIS, g);
-    if constexpr (ZCfgS<T, N>::ok) {
+    const dim3 grid((unsigned)fused_workgroups<T, N, AXIS>(g), 1u, (unsigned)nm);
+    const MemberDesc<T>* d = (const MemberDesc<T>*)md;
+    if constexpr (WideSel<T, N>::compiled) {
+        using W = WideSel<T, N>;
+        if (W::use(g, a.n_outer)) {
+            hipLaunchKernelGGL((k_fused_wide<T, typename W::P, MODE>), grid, dim3(W::C::NT), 0, st, d, g.M, a.n_outer,
+                               W::tiles(g, 1), a.pstride, a.ostride, g.cs(), (const cpx<T>*)tw, want_inv);
+            return;
+        }
+    }
+    if constexpr (WideSel<T, N>::always) {
+        return;
+    } else if constexpr (ZCfgS<T, N>::ok) {
         using C = ZCfgS<T, N>;
         const int ntx = (g.M + C::B - 1) / C::B;
-        const dim3 grid((unsigned)fused_workgroups<T, N, AXIS>(g), 1u, (unsigned)nm);
         const dim3 block(2 * C::P::T * C::B);
-        hipLaunchKernelGGL((k_fused_split<T, typename C::P, C::B, MODE, AXIS>), grid, block, 0, st,
-                           (const MemberDesc<T>*)md, g.M, a.n_outer, ntx, a.pstride, a.ostride, g.cs(),
-                           (const cpx<T>*)tw, want_inv);
+        hipLaunchKernelGGL((k_fused_split<T, typename C::P, C::B, MODE, AXIS>), grid, block, 0, st, d, g.M, a.n_outer,
+                           ntx, a.pstride, a.ostride, g.cs(), (const cpx<T>*)tw, want_inv);
     } else {
         using C = ZCfg<T, N>;
         const int ntx = (g.M + C::B - 1) / C::B;
-        const dim3 grid((unsigned)fused_workgroups<T, N, AXIS>(g), 1u, (unsigned)nm);
         const dim3 block(C::P::T * C::B);
-        hipLaunchKernelGGL((k_fused<T, typename C::P, C::B, MODE, AXIS>), grid, block, 0, st,
-                           (const MemberDesc<T>*)md, g.M, a.n_outer, ntx, a.pstride, a.ostride, g.cs(),
-                           (const cpx<T>*)tw, want_inv);
+        hipLaunchKernelGGL((k_fused<T, typename C::P, C::B, MODE, AXIS>), grid, block, 0, st, d, g.M, a.n_outer, ntx,
+                           a.pstride, a.ostride, g.cs(), (const cpx<T>*)tw, want_inv);
     }
 }
 

@@ -41,7 +41,7 @@ OUT_JSON = os.path.join(ROOT, "profiles", "traffic_256cubed.json")
 
 
 # the sources that define the step's kernels and their launch shapes
-KERNEL_SOURCES = ("fft_core.h", "kernels.h", "small_plane.h", "xz_plane.h", "passes.h", "passes_impl.h",
+KERNEL_SOURCES = ("fft_core.h", "kernels.h", "small_plane.h", "xz_plane.h", "fused_wide.h", "passes.h", "passes_impl.h",
                   "passes_f64.hip", "passes_f32.hip", "passes_c2c_f64.hip", "passes_c2c_f32.hip",
                   *(f"passes_xz_{p}_{m}.hip" for p in ("f64", "f32") for m in ("short", "mid", "long")))
 
