@@ -214,8 +214,8 @@ typedef struct eifp_server eifp_server; /* opaque, owned by the library */
 
 enum {
     EIFP_SERVER_DRY_RUN = 1,  /* schedule only: no device memory, no kernels (host tests) */
-    EIFP_SERVER_NO_GRAPHS = 2,/* launch kernels one by one instead of replaying a captured
-                                 HIP graph per (shape, batch size) */
+    EIFP_SERVER_NO_GRAPHS = 2,/* launch kernels one by one, not as HIP graphs: the only way
+                                 chunks are run, with or without the flag */
     EIFP_SERVER_SERIAL = 4    /* at most one solve on the device at a time (baseline) */
 };
 
@@ -290,8 +290,8 @@ eifp_status eifp_server_create(eifp_server **out, long long hbm_budget_bytes, in
 /* Device bytes one request of this shape holds while admitted: its state, plus an equal
  * snapshot buffer unless EIFP_REQ_NO_SNAPSHOT, plus an equal spectrum buffer with
  * EIFP_REQ_ANCHORED, plus, for a request without EIFP_REQ_ANCHORED whose state is 64 MiB
- * or more, an equal work buffer (its batches then run the x inverse of a step and the x
- * forward of the next as one kernel).  0 for an invalid shape or precision. */
+ * or more, an equal work buffer (smaller ones transform in place).  0 for an invalid shape
+ * or precision. */
 long long eifp_server_footprint(int nx, int ny, int nz, eifp_precision prec, int flags);
 
 /* Queue a solve; the fields are copied before returning.  *req_id receives its id.

@@ -65,19 +65,18 @@ struct Engine {
     // room for the extended record (INV_XPART doubles per workgroup)
     size_t partial_bytes() const { return (size_t)nrec * INV_XPART * sizeof(double); }
 
-    // One step (mode Z_STEP: x, z, fused y, z^-1 with the finalize, x^-1) or a forward-only
-    // evaluation of the invariants (mode Z_FORWARD, or Z_FORWARD_EXT for the extended
-    // record: state -> work, nothing stored back),
-    // for nm members described by the device array md.  ev: 7 events recorded around
-    // the kernels (or null).  want_inv = false skips the invariant partial sums and the
-    // finalize (a step between output points).
-    eifp_status passes(int mode, const void* md, int nm, hipStream_t st, hipEvent_t* ev, bool want_inv = true) const;
-    // nsteps steps (mode Z_STEP), 7 events per step in ev (or null); steps n >= inv_from
-    // reduce the invariants (0: every step; nsteps: none).  combine_x (only with
-    // work != state for every member): the x inverse of a step and the x forward of the
-    // next run as one kernel, which reads the state once instead of twice.
-    eifp_status steps(const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev, long long inv_from,
-                      bool combine_x) const;
+    // Forward-only evaluation of the invariants (mode Z_FORWARD, or Z_FORWARD_EXT for the
+    // extended record: state -> work, nothing stored back), for nm members described by the
+    // device array md.
+    eifp_status forward_invariants(int mode, const void* md, int nm, hipStream_t st) const;
+    // nsteps steps for nm members: x forward and z forward, fused y, z inverse (with the
+    // finalize) and x inverse; between two steps the x inverse and the next x forward (or,
+    // with the plane pass, all four transforms) are one kernel, in place on work, so only
+    // the last step writes the state.  work may be state.  ev: 7 events per step recorded
+    // around the kernels (or null); steps n >= inv_from reduce the invariants (0: every
+    // step; nsteps: none).
+    eifp_status steps(const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev,
+                      long long inv_from) const;
     // unscaled forward transform of each member's state into its work buffer
     eifp_status forward_spectrum(const void* md, int nm, hipStream_t st) const;
     // Jump: each member's state becomes the exact flow over its tau of its anchored

@@ -84,69 +84,35 @@ eifp_status run_plane_middle(const Engine& en, const void* md, int nm, hipStream
 }
 
 template <typename T>
-eifp_status run_passes(const Engine& en, int mode, const void* md, int nm, hipStream_t st, hipEvent_t* ev,
-                       bool want_inv) {
+eifp_status run_forward_invariants(const Engine& en, int mode, const void* md, int nm, hipStream_t st) {
     int rc;
-    if (mode == Z_STEP && use_plane<T>(en)) {
-        if (ev) EIFP_HIP_TRY(hipEventRecord(ev[0], st));
+    if (use_xz<T>(en)) {
+        if ((rc = launch_xz<T>(X_FWD, en.g, md, nm, en.twx, en.twz, st))) return rc_to_status(rc, "x and z forward");
+    } else {
         if ((rc = launch_x<T>(X_FWD, en.g, md, nm, en.twx, st))) return rc_to_status(rc, "x forward");
-        if (ev) EIFP_HIP_TRY(hipEventRecord(ev[1], st));
-        eifp_status s = run_plane_middle<T>(en, md, nm, st, ev, want_inv);
-        if (s) return s;
-        if ((rc = launch_x<T>(X_INV, en.g, md, nm, en.twx, st, want_inv ? en.g.M : 0)))
-            return rc_to_status(rc, "x inverse");
-        if (ev) {
-            EIFP_HIP_TRY(hipEventRecord(ev[5], st));
-            EIFP_HIP_TRY(hipEventRecord(ev[6], st));
-        }
-        return EIFP_OK;
+        if ((rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st))) return rc_to_status(rc, "z forward");
     }
-    const bool xz = use_xz<T>(en);
-    if (ev) EIFP_HIP_TRY(hipEventRecord(ev[0], st));
-    if ((rc = xz ? launch_xz<T>(X_FWD, en.g, md, nm, en.twx, en.twz, st) : launch_x<T>(X_FWD, en.g, md, nm, en.twx, st)))
-        return rc_to_status(rc, "x forward");
-    if (ev) EIFP_HIP_TRY(hipEventRecord(ev[1], st));
-    if (!xz && (rc = launch_c2c<T>(false, AXIS_Z, en.g, md, nm, en.twz, st))) return rc_to_status(rc, "z forward");
-    if (ev) EIFP_HIP_TRY(hipEventRecord(ev[2], st));
-    if ((rc = launch_fused<T>(mode, AXIS_Y, en.g, md, nm, en.twy, want_inv ? 1 : 0, st)))
-        return rc_to_status(rc, "fused y pass");
-    if (ev) EIFP_HIP_TRY(hipEventRecord(ev[3], st));
-    if (mode == Z_STEP) {
-        // the z inverse also finalizes the invariant partials (one extra workgroup per member)
-        const int fin = want_inv ? en.nparts : 0;
-        if (!xz && (rc = launch_c2c<T>(true, AXIS_Z, en.g, md, nm, en.twz, st, fin)))
-            return rc_to_status(rc, "z inverse");
-        if (ev) EIFP_HIP_TRY(hipEventRecord(ev[4], st));
-        if ((rc = xz ? launch_xz<T>(X_INV, en.g, md, nm, en.twx, en.twz, st, fin)
-                     : launch_x<T>(X_INV, en.g, md, nm, en.twx, st)))
-            return rc_to_status(rc, "x inverse");
-        if (ev) EIFP_HIP_TRY(hipEventRecord(ev[5], st));
-    } else if (ev) {
-        EIFP_HIP_TRY(hipEventRecord(ev[4], st));
-        EIFP_HIP_TRY(hipEventRecord(ev[5], st));
-    }
-    if (mode != Z_STEP && want_inv && (rc = launch_finalize<T>(md, nm, en.nparts, st, mode == Z_FORWARD_EXT)))
-        return rc_to_status(rc, "finalize");
-    if (ev) EIFP_HIP_TRY(hipEventRecord(ev[6], st));
+    if ((rc = launch_fused<T>(mode, AXIS_Y, en.g, md, nm, en.twy, 1, st))) return rc_to_status(rc, "fused y pass");
+    if ((rc = launch_finalize<T>(md, nm, en.nparts, st, mode == Z_FORWARD_EXT))) return rc_to_status(rc, "finalize");
     return EIFP_OK;
 }
 
-// nsteps steps; steps n >= inv_from reduce the invariants.  With work != state, the x
-// inverse of each step but the last and the x forward of the step after it run as one
-// kernel (X_INVFWD, in place on work: the state buffer is written by the last step
-// only), and the z forward pass after it takes the components in ascending order.
-// Events per step as in run_passes (the x forward slot is empty after the first step;
-// the x inverse slot holds the combined kernel).  Grids with a plane pass run it in
-// place of the three middle passes (use_plane).
+// nsteps steps; steps n >= inv_from reduce the invariants.  The x inverse of each step but
+// the last and the x forward of the step after it run as one kernel (X_INVFWD, in place on
+// work: the state buffer, if another, is written by the last step only), and the z forward
+// pass after it takes the components in ascending order.  Events per step: before and after
+// the x forward (empty after the first step), z forward, fused, z inverse and x inverse
+// (which holds the combined kernel) slots, and one more.  Grids with a plane pass run it in
+// place of the three middle passes (use_plane) or of the four around the fused one (use_xz).
 template <typename T>
 eifp_status run_steps(const Engine& en, const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev,
-                      long long inv_from, bool combine_x) {
+                      long long inv_from) {
     int rc;
     const bool plane = use_plane<T>(en), xz = !plane && use_xz<T>(en);
     for (long long n = 0; n < nsteps; ++n) {
         const bool want_inv = n >= inv_from;
         hipEvent_t* e = ev ? ev + 7 * n : nullptr;
-        const bool first = n == 0 || !combine_x, last = n + 1 == nsteps || !combine_x;
+        const bool first = n == 0, last = n + 1 == nsteps;
         if (e) EIFP_HIP_TRY(hipEventRecord(e[0], st));
         if (first && (rc = xz ? launch_xz<T>(X_FWD, en.g, md, nm, en.twx, en.twz, st)
                               : launch_x<T>(X_FWD, en.g, md, nm, en.twx, st)))
@@ -309,9 +275,9 @@ void Engine::release() {
     twx = twy = twz = nullptr;
 }
 
-eifp_status Engine::passes(int mode, const void* md, int nm, hipStream_t st, hipEvent_t* ev, bool want_inv) const {
-    return prec == EIFP_FP64 ? run_passes<double>(*this, mode, md, nm, st, ev, want_inv)
-                             : run_passes<float>(*this, mode, md, nm, st, ev, want_inv);
+eifp_status Engine::forward_invariants(int mode, const void* md, int nm, hipStream_t st) const {
+    return prec == EIFP_FP64 ? run_forward_invariants<double>(*this, mode, md, nm, st)
+                             : run_forward_invariants<float>(*this, mode, md, nm, st);
 }
 
 eifp_status Engine::forward_spectrum(const void* md, int nm, hipStream_t st) const {
@@ -319,9 +285,9 @@ eifp_status Engine::forward_spectrum(const void* md, int nm, hipStream_t st) con
 }
 
 eifp_status Engine::steps(const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev,
-                          long long inv_from, bool combine_x) const {
-    return prec == EIFP_FP64 ? run_steps<double>(*this, md, nm, nsteps, st, ev, inv_from, combine_x)
-                             : run_steps<float>(*this, md, nm, nsteps, st, ev, inv_from, combine_x);
+                          long long inv_from) const {
+    return prec == EIFP_FP64 ? run_steps<double>(*this, md, nm, nsteps, st, ev, inv_from)
+                             : run_steps<float>(*this, md, nm, nsteps, st, ev, inv_from);
 }
 
 eifp_status Engine::jump(const void* md, int nm, hipStream_t st, bool want_inv) const {

@@ -144,9 +144,9 @@ eifp_status step_noalloc(void* fields, int nx, int ny, int nz, const eifp_domain
     hipLaunchKernelGGL((k_noalloc_setup<T>), dim3((unsigned)((nmax + 255) / 256), 3u), dim3(256), 0, st, d,
                        (DescImage*)(b + L.desc), (cpx<T>*)en.twx, nx, (cpx<T>*)en.twy, ny, (cpx<T>*)en.twz, nz);
     if (hipGetLastError() != hipSuccess) return fail(EIFP_ERR_DEVICE, "set-up kernel launch failed");
-    // in place (work == state): one x forward and one x inverse kernel per step; the
-    // invariants are reduced on the last step only, and only when asked for
-    return en.steps(b + L.desc, 1, nsteps, st, nullptr, inv_out ? nsteps - 1 : nsteps, false);
+    // in place (work == state); the invariants are reduced on the last step only, and only
+    // when asked for
+    return en.steps(b + L.desc, 1, nsteps, st, nullptr, inv_out ? nsteps - 1 : nsteps);
 }
 
 }  // namespace

@@ -2,9 +2,8 @@
 //
 // Requests are grouped by (nx, ny, nz, precision).  A group owns the executor for its
 // shape (twiddle tables), one stream, and a device array of member descriptors; one
-// chunk of k steps of the whole group is k launches of the five-pass step (or k
-// replays of a HIP graph captured for the group's current batch size), so every
-// member advances by k steps in the same kernels.  Members join and leave between
+// chunk of k steps of the whole group is one launch sequence of k steps (Engine::steps),
+// so every member advances by k steps in the same kernels.  Members join and leave between
 // chunks.  k stops at the next output point of any member and is capped so that a
 // chunk lasts a few milliseconds, which bounds how long an arrival waits to join.
 // Groups of different shapes live on different streams, so their chunks overlap on
@@ -99,7 +98,6 @@ struct Group {
     bool in_flight = false;
     int k = 0;                       // steps in flight
     int nm_flight = 0;
-    std::map<std::pair<int, bool>, hipGraphExec_t> graphs;  // (batch size, with invariants)
     double ms_per_member_step = 0;   // running estimate
     int readers = 0;
 };
@@ -123,14 +121,11 @@ long long group_bytes_of(const Key& k, int max_batch) {
 }
 
 // Stepped requests whose state is at least this large transform in a work buffer of
-// their own, so that a chunk's steps run the x inverse of one step and the x forward of
-// the next as one kernel (one read of the state fewer per step); their chunks are
-// enqueued kernel by kernel, which costs nothing next to kernels of this size.  Smaller
-// requests step in place from captured one-step graphs.
-constexpr long long kCombineBytes = 64LL << 20;
+// their own (counted in eifp_server_footprint); smaller ones transform in place.
+constexpr long long kWorkBytes = 64LL << 20;
 
 bool uses_work(long long state_bytes, int flags) {
-    return !(flags & EIFP_REQ_ANCHORED) && state_bytes >= kCombineBytes;
+    return !(flags & EIFP_REQ_ANCHORED) && state_bytes >= kWorkBytes;
 }
 
 long long footprint_of(int nx, int ny, int nz, int prec, int flags) {
@@ -191,8 +186,6 @@ namespace {
 void group_free(Group* g) {
     if (!g) return;
     if (g->st) (void)hipStreamSynchronize(g->st);
-    for (auto& kv : g->graphs) (void)hipGraphExecDestroy(kv.second);
-    g->graphs.clear();
     for (void* p : {g->desc_dev, (void*)g->partials, (void*)g->inv_dev})
         if (p) (void)hipFree(p);
     if (g->desc_host) (void)hipHostFree(g->desc_host);
@@ -450,22 +443,6 @@ long long next_boundary(const Req* r) {
     return b;
 }
 
-eifp_status capture_step_graph(Group* g, int nm, bool want_inv, hipGraphExec_t* out) {
-    hipGraph_t graph = nullptr;
-    EIFP_HIP_TRY(hipStreamBeginCapture(g->st, hipStreamCaptureModeThreadLocal));
-    const eifp_status st = g->en.passes(Z_STEP, g->desc_dev, nm, g->st, nullptr, want_inv);
-    const hipError_t e = hipStreamEndCapture(g->st, &graph);
-    if (st) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return st;
-    }
-    if (e != hipSuccess) return fail(EIFP_ERR_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-    const hipError_t ei = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (ei != hipSuccess) return fail(EIFP_ERR_DEVICE, "graph instantiate failed: %s", hipGetErrorString(ei));
-    return EIFP_OK;
-}
-
 // A chunk of a jump group: members not yet anchored get their spectrum stored (forward
 // transform into spec, through the second descriptor region), then every member jumps
 // from its anchor to its own next output point (descriptor region one, rewritten each
@@ -541,30 +518,11 @@ eifp_status launch_chunk(eifp_server* sv, Group* g) {
         bool out_at_end = false;
         for (Req* r : g->members) out_at_end |= r->done + k == next_boundary(r);
         EIFP_HIP_TRY(hipEventRecord(g->ev0, g->st));
-        const bool combine = uses_work(state_bytes_of(g->key.nx, g->key.ny, g->key.nz, g->key.prec), 0);
-        if (combine) {
-            // every member has a work buffer: the chunk's steps as one sequence, the x
-            // inverse of a step and the x forward of the next as one kernel
-            eifp_status st = g->en.steps(g->desc_dev, nm, k, g->st, nullptr, out_at_end ? k - 1 : k, true);
-            if (st) return st;
-        }
-        for (long long s = 0; s < (combine ? 0 : k); ++s) {
-            const bool inv = out_at_end && s == k - 1;
-            if (sv->flags & EIFP_SERVER_NO_GRAPHS) {
-                eifp_status st = g->en.passes(Z_STEP, g->desc_dev, nm, g->st, nullptr, inv);
-                if (st) return st;
-                continue;
-            }
-            hipGraphExec_t& ge = g->graphs[std::make_pair(nm, inv)];
-            if (!ge) {
-                eifp_status st = capture_step_graph(g, nm, inv, &ge);
-                if (st) {
-                    g->graphs.erase(std::make_pair(nm, inv));
-                    return st;
-                }
-            }
-            EIFP_HIP_TRY(hipGraphLaunch(ge, g->st));
-        }
+        // the chunk's steps as one sequence: the intermediate states stay in the spectral
+        // buffer, the last step leaves the state (us per step, against one-step graphs of
+        // the separate passes: one 32^3 FP64 solve 21 -> 14, six mixed small ones 142 -> 69)
+        const eifp_status st = g->en.steps(g->desc_dev, nm, k, g->st, nullptr, out_at_end ? k - 1 : k);
+        if (st) return st;
         for (Req* r : g->members)
             if (r->snap && r->done + k == next_boundary(r) && r->done + k < r->rq.nsteps)
                 EIFP_HIP_TRY(hipMemcpyAsync(r->snap, r->state, r->state_bytes, hipMemcpyDeviceToDevice, g->st));

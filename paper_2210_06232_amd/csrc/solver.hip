@@ -209,7 +209,7 @@ static eifp_status step_impl(eifp_solver* s, double tau, long long nsteps, doubl
             s->events.push_back(e);
         }
     }
-    if ((st = s->en.steps(step_desc(s), 1, nsteps, s->stream, pass_ms ? s->events.data() : nullptr, 0, true)))
+    if ((st = s->en.steps(step_desc(s), 1, nsteps, s->stream, pass_ms ? s->events.data() : nullptr, 0)))
         return st;
     s->t += tau * (double)nsteps;
     s->steps += nsteps;
@@ -265,7 +265,7 @@ eifp_status eifp_invariants(eifp_solver* s, eifp_invariant_set* out) {
     clear_error();
     if (!s || !out) return fail(EIFP_ERR_INVALID_ARG, "NULL argument");
     if (!s->inv_current) {
-        const eifp_status st = s->en.passes(Z_FORWARD, fwd_desc(s), 1, s->stream, nullptr);
+        const eifp_status st = s->en.forward_invariants(Z_FORWARD, fwd_desc(s), 1, s->stream);
         if (st != EIFP_OK) return st;
         s->inv_current = true;
     }
@@ -289,7 +289,7 @@ eifp_status eifp_invariants(eifp_solver* s, eifp_invariant_set* out) {
 eifp_status eifp_invariants_ext(eifp_solver* s, eifp_invariant_ext_set* out) {
     clear_error();
     if (!s || !out) return fail(EIFP_ERR_INVALID_ARG, "NULL argument");
-    eifp_status st = s->en.passes(Z_FORWARD_EXT, fwd_desc(s), 1, s->stream, nullptr);
+    eifp_status st = s->en.forward_invariants(Z_FORWARD_EXT, fwd_desc(s), 1, s->stream);
     if (st != EIFP_OK) return st;
     s->inv_current = true;  // the basic record is rewritten for the same state
     EIFP_HIP_TRY(hipMemcpyAsync(s->inv_host, s->inv_dev, INV_XPART * sizeof(double), hipMemcpyDeviceToHost, s->stream));
