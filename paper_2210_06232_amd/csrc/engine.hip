@@ -39,20 +39,24 @@ eifp_status rc_to_status(int rc, const char* what) {
     return fail(EIFP_ERR_DEVICE, "%s: kernel launch failed: %s", what, hipGetErrorString(hipGetLastError()));
 }
 
-// Grids whose (y, z) plane fits in LDS step with the plane pass in place of the z
-// forward, fused y and z inverse passes (the partial records it writes, one per packed
-// x column, must fit the member's partials buffer, which every caller sizes for
-// partial_capacity records); the x kernel after it finalizes.
-template <typename T>
-bool use_plane(const Engine& en) {
-    return plane_ok<T>(en.g) && en.g.M <= en.nrec;
-}
-
 // Grids whose (x, z) plane of one component fits in LDS run the z and x transforms
 // between two fused passes as one kernel.
 template <typename T>
 bool use_xz(const Engine& en) {
     return xz_ok<T>(en.g);
+}
+
+// Of the others (Nx below 16 or Nz below 8, or a plane too large), those whose (y, z) plane
+// of all six components fits in LDS step with the plane pass in place of the z forward,
+// fused y and z inverse passes (the partial records it writes, one per packed x column,
+// must fit the member's partials buffer, which every caller sizes for partial_capacity
+// records); the x kernel after it finalizes.  Where both are compiled the (x, z) plane is
+// faster, having Ny times six workgroups instead of Nx/2 (us per FP64 step, (y, z) / (x, z)
+// plane: 16^3 13.6 / 12.0, 32x16x16 16.3 / 12.6, 24^3 23.8 / 14.6, 256x24x24 34.8 / 24.1);
+// without the latter a (y, z) plane beats the separate passes (8^3 10.1 / 19.0).
+template <typename T>
+bool use_plane(const Engine& en) {
+    return plane_ok<T>(en.g) && !use_xz<T>(en) && en.g.M <= en.nrec;
 }
 
 }  // namespace
@@ -108,7 +112,7 @@ template <typename T>
 eifp_status run_steps(const Engine& en, const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev,
                       long long inv_from) {
     int rc;
-    const bool plane = use_plane<T>(en), xz = !plane && use_xz<T>(en);
+    const bool xz = use_xz<T>(en), plane = use_plane<T>(en);
     for (long long n = 0; n < nsteps; ++n) {
         const bool want_inv = n >= inv_from;
         hipEvent_t* e = ev ? ev + 7 * n : nullptr;

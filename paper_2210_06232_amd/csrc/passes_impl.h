@@ -424,10 +424,9 @@ inline bool plane_len(int n) {
     }
 }
 // Plane pass only where it is the faster path: planes of up to 576 points, where a
-// step is dominated by the per-launch cost (us per FP64 step, plane / strided: 8^3 9.7 /
-// 21.6, 16^3 13.7 / 25.2, 256 x 16^2 22.5 / 33.6, 32 x 16 x 32 23.0 / 29.0, 24^3 23.9 /
-// 24.6).  A 32 x 32 plane is 13% slower than the strided passes: its workgroup takes a
-// whole CU and only M of them run.
+// step is dominated by the per-launch cost (us per FP64 step, plane / separate passes: 4^3
+// 9.3 / 17.1, 8^3 10.1 / 19.0, 8x24x24 21.0 / 20.4, 128x4x4 13.0 / 21.4).  A 32 x 32 plane is
+// slower: its workgroup takes a whole CU and only M of them run.
 #ifndef EIFP_PLANE_MAX_POINTS
 #define EIFP_PLANE_MAX_POINTS 576
 #endif

@@ -27,7 +27,9 @@ DOMAIN = (0.0, 2 * math.pi, -1.0, 4 * math.pi - 1.0, 0.5, 2.5)
 # fewer planes than CUs and with more (several planes a workgroup, FP64); planes of FP32
 # at the two-workgroups-a-CU limit and just beyond it (separate passes)
 XZ_SHAPES = [(16, 96, 8), (24, 64, 12), (48, 32, 32), (48, 96, 8), (16, 4, 512), (512, 6, 16), (192, 8, 96),
-             (128, 32, 128), (128, 48, 128), (96, 48, 192), (192, 16, 64), (128, 8, 192)]
+             (128, 32, 128), (128, 48, 128), (96, 48, 192), (192, 16, 64), (128, 8, 192),
+             # the smallest grid of the pass, and its neighbours that take the (y, z) plane
+             (16, 4, 8), (12, 4, 8), (16, 4, 6), (256, 8, 6)]
 
 
 def eifp():
