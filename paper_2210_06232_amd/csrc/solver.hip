@@ -40,8 +40,7 @@ struct eifp_solver {
     void* anchor = nullptr;      // anchored spectrum (allocated on first use)
     bool anchor_valid = false;
     double t_anchor = 0.0;
-    void* desc_dev = nullptr;    // DescImage[4]
-    DescImage desc_host[4]{};
+    void* desc_dev = nullptr;    // DescImage[D_COUNT]
     double desc_tau = 0.0;       // tau held by desc_dev[0]
     double jump_span = 0.0;      // time span held by desc_dev[3]
     bool inv_current = false;    // inv_dev describes the current state
@@ -75,40 +74,42 @@ eifp_status alloc(void** p, size_t n, long long* bytes) {
     return EIFP_OK;
 }
 
-// Write the descriptors for step size tau and jump span `span`.  The copy is
-// synchronous with respect to the host buffer (the stream is drained first), so it
-// only happens when tau or the span changes.
-eifp_status upload_desc(eifp_solver* s, double tau, double span) {
+// Write one descriptor, in stream order: the image travels as the kernel's argument, so
+// nothing waits for the work before it (a copy from desc_host would have to; a jump of 64 x
+// 128 x 256 FP32, whose span changes with every call, 111 -> 101 us with the fields and
+// invariants read out).
+__global__ void k_write_desc(DescImage d, DescImage* __restrict__ out) {
+    if (threadIdx.x == 0) *out = d;
+}
+
+enum { D_STEP = 0, D_FWD = 1, D_ANCHOR = 2, D_JUMP = 3, D_COUNT = 4 };
+
+// Descriptor i, for a time span of `span` (the step size, or what a jump covers).  Steps
+// transform in the scratch buffer, so the state is written by a call's last step only.
+eifp_status write_desc(eifp_solver* s, int i, double span) {
     const Grid3& g = s->en.g;
-    const PropParams p0 = make_params(g.nx, g.ny, g.nz, s->dom, s->mu, s->eps, 0.0);
-    // steps transform in the scratch buffer (the x inverse of a step and the x forward
-    // of the next then run as one kernel)
-    s->desc_host[0] = DescImage{s->state, s->scratch, s->partials, s->inv_dev, nullptr,
-                                make_params(g.nx, g.ny, g.nz, s->dom, s->mu, s->eps, tau)};
-    s->desc_host[1] = DescImage{s->state, s->scratch, s->partials, s->inv_dev, nullptr, p0};
-    s->desc_host[2] = DescImage{s->state, s->anchor, s->partials, s->inv_dev, nullptr, p0};
-    s->desc_host[3] = DescImage{s->state, s->state, s->partials, s->inv_dev, s->anchor,
-                                make_params(g.nx, g.ny, g.nz, s->dom, s->mu, s->eps, span)};
-    EIFP_HIP_TRY(hipStreamSynchronize(s->stream));
-    EIFP_HIP_TRY(hipMemcpyAsync(s->desc_dev, s->desc_host, sizeof s->desc_host, hipMemcpyHostToDevice, s->stream));
-    EIFP_HIP_TRY(hipStreamSynchronize(s->stream));
-    s->desc_tau = tau;
-    s->jump_span = span;
+    void* work = i == D_ANCHOR ? s->anchor : (i == D_JUMP ? s->state : s->scratch);
+    const DescImage d{s->state, work, s->partials, s->inv_dev, i == D_JUMP ? s->anchor : nullptr,
+                      make_params(g.nx, g.ny, g.nz, s->dom, s->mu, s->eps, span)};
+    hipLaunchKernelGGL(k_write_desc, dim3(1), dim3(64), 0, s->stream, d, (DescImage*)s->desc_dev + i);
+    if (hipGetLastError() != hipSuccess) return fail(EIFP_ERR_DEVICE, "descriptor kernel launch failed");
+    if (i == D_STEP) s->desc_tau = span;
+    if (i == D_JUMP) s->jump_span = span;
     return EIFP_OK;
 }
 
 const void* desc_at(const eifp_solver* s, int i) { return (const char*)s->desc_dev + i * sizeof(DescImage); }
-const void* step_desc(const eifp_solver* s) { return desc_at(s, 0); }
-const void* fwd_desc(const eifp_solver* s) { return desc_at(s, 1); }
+const void* step_desc(const eifp_solver* s) { return desc_at(s, D_STEP); }
+const void* fwd_desc(const eifp_solver* s) { return desc_at(s, D_FWD); }
 
 // Store the spectrum of the current state as the anchor (time t).
 eifp_status make_anchor(eifp_solver* s) {
     eifp_status st;
     if (!s->anchor) {
         if ((st = alloc(&s->anchor, s->en.state_bytes(), &s->bytes))) return st;
-        if ((st = upload_desc(s, s->desc_tau, s->jump_span))) return st;
+        if ((st = write_desc(s, D_ANCHOR, 0.0)) || (st = write_desc(s, D_JUMP, 0.0))) return st;
     }
-    if ((st = s->en.forward_spectrum(desc_at(s, 2), 1, s->stream))) return st;
+    if ((st = s->en.forward_spectrum(desc_at(s, D_ANCHOR), 1, s->stream))) return st;
     s->anchor_valid = true;
     s->t_anchor = s->t;
     return EIFP_OK;
@@ -165,9 +166,10 @@ eifp_status eifp_init(eifp_solver** out, int nx, int ny, int nz, const eifp_doma
     INIT_TRY(alloc(&s->scratch, sb, &s->bytes));
     INIT_TRY(alloc((void**)&s->partials, s->en.partial_bytes(), &s->bytes));
     INIT_TRY(alloc((void**)&s->inv_dev, INV_XPART * sizeof(double), &s->bytes));
-    INIT_TRY(alloc(&s->desc_dev, sizeof s->desc_host, &s->bytes));
+    INIT_TRY(alloc(&s->desc_dev, D_COUNT * sizeof(DescImage), &s->bytes));
     INIT_HIP(hipHostMalloc((void**)&s->inv_host, INV_XPART * sizeof(double), hipHostMallocDefault));
-    INIT_TRY(upload_desc(s, 0.0, 0.0));
+    INIT_TRY(write_desc(s, D_STEP, 0.0));
+    INIT_TRY(write_desc(s, D_FWD, 0.0));
     // upload: FP64 directly; FP32 through the scratch buffer (3 ns doubles = 6 ns floats)
     const size_t half = (size_t)3 * ns * sizeof(double);
     if (prec == EIFP_FP64) {
@@ -199,7 +201,7 @@ static eifp_status step_impl(eifp_solver* s, double tau, long long nsteps, doubl
             for (int i = 0; i < 6; ++i) pass_ms[i] = 0.0;
         return EIFP_OK;
     }
-    if (tau != s->desc_tau && (st = upload_desc(s, tau, s->jump_span))) return st;
+    if (tau != s->desc_tau && (st = write_desc(s, D_STEP, tau))) return st;
     s->anchor_valid = false;  // the state no longer follows from the anchor
     if (pass_ms) {
         const size_t need = (size_t)7 * (size_t)nsteps;
@@ -248,8 +250,8 @@ eifp_status eifp_jump(eifp_solver* s, double tau, long long nsteps) {
     const double t_new = s->t + tau * (double)nsteps;
     const double span = t_new - s->t_anchor;
     if (!std::isfinite(span)) return fail(EIFP_ERR_INVALID_ARG, "time span is not finite");
-    if (span != s->jump_span && (st = upload_desc(s, s->desc_tau, span))) return st;
-    if ((st = s->en.jump(desc_at(s, 3), 1, s->stream))) return st;
+    if (span != s->jump_span && (st = write_desc(s, D_JUMP, span))) return st;
+    if ((st = s->en.jump(desc_at(s, D_JUMP), 1, s->stream))) return st;
     s->t = t_new;
     s->steps += nsteps;
     s->inv_current = true;
