@@ -472,12 +472,21 @@ int launch_plane(const Grid3& g, const void* md, int nm, const void* twy, const 
 // FP32, where the work is issue-bound, only while two workgroups share a CU (us per step,
 // separate passes / plane pass, Ny = 64: 192x64x64 FP32 68.0 / 52.8, 128x64x192 84.5 /
 // 86.7, 64x64x512 109 / 121; FP64 192x64x96 131 / 115, 128x64x128 99 / 71).
+// Values per thread of the plane pass: as the separate passes on large planes (fewest
+// stages); 8, or 4 at length 16, on small ones, where twice or four times the waves, each
+// with a half or a quarter of the serial work, count for more (us per step, 16 values / 8:
+// 64^3 FP64 31.1 / 28.5, 32^3 FP64 14.9 / 13.5, 64^3 FP32 22.2 / 20.2, 64x64x128 FP64 39.0 /
+// 37.7; but 128x64x64 FP32 33.9 / 34.5 and 128^3 FP64 95 / 150).
+template <typename T, int N, int PLANE> struct XZE {
+    static constexpr bool small = PLANE <= (sizeof(T) == 8 ? 4096 : 2048);
+    static constexpr int E = !small ? XYE<N>::E : N == 16 ? 4 : N == 32 || N == 64 ? 8 : XYE<N>::E;
+};
 template <typename T, int M, int N> struct XzPair {
     static constexpr bool ok() {
         if constexpr (M < 8 || N < 8 || M * N > 10240) {
             return false;
         } else {
-            using C = XzCfg<T, Plan<N, XYE<N>::E>, Plan<M, XYE<M>::E>>;
+            using C = XzCfg<T, Plan<N, XZE<T, N, M * N>::E>, Plan<M, XZE<T, M, M * N>::E>>;
             return C::lds_bytes <= (sizeof(T) == 4 ? C::HALF : C::FULL);
         }
     }
@@ -485,8 +494,8 @@ template <typename T, int M, int N> struct XzPair {
 template <typename T, int M, int N>
 int run_xz(int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz, hipStream_t st,
            int fin_nparts) {
-    using PZ = Plan<N, XYE<N>::E>;
-    using PX = Plan<M, XYE<M>::E>;
+    using PZ = Plan<N, XZE<T, N, M * N>::E>;
+    using PX = Plan<M, XZE<T, M, M * N>::E>;
     using C = XzCfg<T, PZ, PX>;
     const int nplanes = 6 * g.ny;
     int nwg = nplanes;
