@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "engine.h"
+#include "host_copy.h"
 
 using namespace eifp;
 
@@ -129,9 +130,8 @@ eifp_status eifp_init(eifp_solver** out, int nx, int ny, int nz, const eifp_doma
     if ((st = validate_shape(nx, ny, nz)) || (st = validate_problem(dom, mu, eps))) return st;
     if (prec != EIFP_FP64 && prec != EIFP_FP32) return fail(EIFP_ERR_INVALID_ARG, "unknown precision %d", (int)prec);
     const long long ns = (long long)nx * ny * nz;
-    for (long long q = 0; q < 3 * ns; ++q)
-        if (!std::isfinite(H0[q]) || !std::isfinite(E0[q]))
-            return fail(EIFP_ERR_NONFINITE, "initial field holds NaN/Inf at flat index %lld", q);
+    const long long bad = std::min(check_finite<double>(H0, nullptr, 3 * ns), check_finite<double>(E0, nullptr, 3 * ns));
+    if (bad < 3 * ns) return fail(EIFP_ERR_NONFINITE, "initial field holds NaN/Inf at flat index %lld", bad);
 
     eifp_solver* s = new (std::nothrow) eifp_solver;
     if (!s) return fail(EIFP_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -319,6 +319,8 @@ eifp_status eifp_fields(eifp_solver* s, double* H, double* E) {
     if (!s || !H || !E) return fail(EIFP_ERR_INVALID_ARG, "NULL argument");
     const long long ns = s->en.ns;
     const size_t half = (size_t)3 * ns * sizeof(double);
+    touch_pages(H, (long long)half);
+    touch_pages(E, (long long)half);
     if (s->en.prec == EIFP_FP64) {
         EIFP_HIP_TRY(hipMemcpyAsync(H, s->state, half, hipMemcpyDeviceToHost, s->stream));
         EIFP_HIP_TRY(hipMemcpyAsync(E, (char*)s->state + half, half, hipMemcpyDeviceToHost, s->stream));
