@@ -119,40 +119,25 @@ k_yz_plane(const MemberDesc<T>* __restrict__ md, int M, long cs, const cpx<T>* _
 }
 
 // The member's basic invariant record from its nparts partial records, by the first wave
-// of a workgroup alone (no barrier, so any block size will do): per-lane compensated
-// sums over records lane, lane + 64, ..., then a fixed butterfly across the lanes.  It
-// writes the record finalize_member writes, its sums taken in another fixed order.
+// of a workgroup alone (no barrier, so any block size will do): lane (r, q) takes sum q of
+// records r, r + 8, ..., then a fixed butterfly across the eight.  It writes the record
+// finalize_member writes, its sums taken in another fixed order.
 __device__ __forceinline__ void finalize_member_wave(const double* __restrict__ partials, int nparts,
                                                      double* __restrict__ out) {
     if (threadIdx.x >= 64) return;
     constexpr int Q = INV_NPART;
-    double s[Q], c[Q];
+    const int q = (int)threadIdx.x % Q;
+    double s = 0.0, c = 0.0;
+#pragma unroll 4
+    for (int j = (int)threadIdx.x / Q; j < nparts; j += 64 / Q) neumaier_add(s, c, partials[(long)j * Q + q]);
 #pragma unroll
-    for (int q = 0; q < Q; ++q) s[q] = c[q] = 0.0;
-    for (int j = threadIdx.x; j < nparts; j += 64) {
-        const double* rec = partials + (long)j * Q;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) neumaier_add(s[q], c[q], rec[q]);
+    for (int off = Q; off < 64; off <<= 1) {
+        const double os = __shfl_xor(s, off, 64), oc = __shfl_xor(c, off, 64);
+        c += oc;
+        neumaier_add(s, c, os);
     }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double os = __shfl_xor(s[q], off, 64), oc = __shfl_xor(c[q], off, 64);
-            c[q] += oc;
-            neumaier_add(s[q], c[q], os);
-        }
-    }
-    if (threadIdx.x == 0) {
-        out[0] = s[INV_E1] + c[INV_E1];
-        out[1] = s[INV_H1] + c[INV_H1];
-        out[2] = s[INV_M1X] + c[INV_M1X];
-        out[3] = s[INV_M1Y] + c[INV_M1Y];
-        out[4] = s[INV_M1Z] + c[INV_M1Z];
-        out[5] = sqrt(s[INV_DIVH] + c[INV_DIVH]);
-        out[6] = sqrt(s[INV_DIVE] + c[INV_DIVE]);
-        out[7] = 0.0;
-    }
+    const double r = s + c;
+    if (threadIdx.x < Q) out[q] = q == INV_DIVH || q == INV_DIVE ? sqrt(r) : (q == Q - 1 ? 0.0 : r);
 }
 
 // The x kernels of a plane step: the last workgroup (one past the row blocks) finalizes
