@@ -7,12 +7,13 @@
 // A pencil lies in one wave, so its exchanges need no barrier, and a thread holds one
 // component's values instead of six (k_fused) or three (k_fused_split): on small grids a
 // tile's six waves fill the device where the other forms' one to four cannot, and in FP64
-// at lengths 96 to 192 the freed registers hold 12 or 16 values a lane (fewer stages) and
+// at lengths 96 to 256 the freed registers hold 12 or 16 values a lane (fewer stages) and
 // the next tile's loads.  The modes ky and -ky of a column are one thread's, which forms
 // the phase and the coefficients once for both (a tenth of the pass's vector instructions).
 //
 // Measured (us, the form replaced / this one): 32^3 FP64 17 / 10, 64^3 FP64 24 / 14 and
-// FP32 19 / 11, 128^3 FP64 54 / 42 (4.8 TB/s), 192^3 FP64 248 / 178 (3.8 TB/s).  Bound by
+// FP32 19 / 11, 128^3 FP64 54 / 42 (4.8 TB/s), 192^3 FP64 248 / 178 (3.8 TB/s), 256^3 FP64
+// 419 / 376 (4.3 TB/s).  Bound by
 // the latency of a load, two barriers and a store on small grids; above, a CU holds one
 // workgroup, whose memory, LDS and arithmetic phases (192^3: 123, 61 and 44 us of the
 // 178) only the loads of the next tile overlap.
@@ -59,6 +60,10 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
     using C = WideCfg<T, P>;
     constexpr int N = P::N, E = P::E, TT = P::T, B = C::B, NT = C::NT, PLANE = C::PLANE;
     constexpr int Q = NQ<MODE>::value;
+    // values of the next tile loaded before the modes; the others after the inverse
+    // transform, where all 16 FP64 values of length 256 beside the transform's would spill
+    // (fused pass of 256^3: all early 480 us, half 378, a quarter 406)
+    constexpr int kEarly = N == 256 && sizeof(T) == 8 && (MODE == Z_STEP || MODE == Z_JUMP) ? E / 2 : E;
     __shared__ cpx<T> s_x[6 * PLANE];
     __shared__ cpx<T> s_tw[N * TwParts<T>::value];
     __shared__ double s_red[(NT / 64) * Q];
@@ -109,7 +114,8 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
         __syncthreads();
         if (C::PERSIST && wn < ntiles) {
             nvoff = voff_of(wn, nactive);
-            load_col<T, P>(nv, rs, nvoff, sstep);
+#pragma unroll
+            for (int i = 0; i < kEarly; ++i) nv[i] = BufIO<T>::ld(rs, nvoff, (unsigned)m_first<P>(i) * sstep);
         }
         // modes, in pairs ky and -ky, which share the phase and the coefficients (the
         // pair 0 is ky = 0 and the Nyquist index, both with Omega_y = 0): thread i takes
@@ -177,6 +183,10 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
             for (int i = 0; i < E; ++i) v[i] = lds.ld(t + TT * m_first<P>(i));
             lds.after_load();
             fft_pencil<P, true, kStagedTw>(v, t, lds, s_tw);
+            if (C::PERSIST && wn < ntiles) {
+#pragma unroll
+                for (int i = kEarly; i < E; ++i) nv[i] = BufIO<T>::ld(rs, nvoff, (unsigned)m_first<P>(i) * sstep);
+            }
             store_col<T, P, EIFP_FUSED_ST_AUX>(v, rd, voff, sstep, active);
         }
         ++k;

@@ -220,17 +220,16 @@ template <typename T, int N> struct WideSel {
     // The largest number of tiles a member may have for this form: -1 none (the length is
     // not compiled), 0 no limit.  With few tiles the form's six waves a tile fill the
     // device where the other forms' one to four cannot; with many the other forms' wider
-    // tiles and fewer LDS passes win, except in FP64 at 64 to 192, where its lower
+    // tiles and fewer LDS passes win, except in FP64 at 64 to 256, where its lower
     // register need (one component instead of six or three a thread) does.  Fused pass,
     // us, other form / this one, FP64: 64^3 (256 tiles) 23.9 / 14.1, 64x32x256 (512) 23.7 /
     // 18.9, 256x32x256 (2048) 48.4 / 52.3, 256x64x256 (4096) 102 / 95, 128^3 55.2 / 43.5,
-    // 192^3 248 / 179, 64x256x256 (2048) 104 / 100, 256^3 (16384) 418 / 480; FP32: 64^3
+    // 192^3 248 / 179, 64x256x256 104 / 76, 256^3 419 / 376; FP32: 64^3
     // 19.0 / 12.4, 96^3 (576) 30.3 / 28.1, 64x192x64 (512) 29.1 / 24.7, 64x64x256 (1024) 27.8
     // / 31.1, 256^3 243 / 433.
     static constexpr int max_tiles = N < 8 || N > 256 || C::lds_bytes > 160 * 1024 ? -1
                                      : sizeof(T) == 4                               ? 640
-                                     : N >= 64 && N <= 192                          ? 0
-                                     : N == 256                                     ? 2048
+                                     : N >= 64                                      ? 0
                                                                                     : 512;
     static constexpr bool compiled = max_tiles >= 0, always = max_tiles == 0;
     static int tiles(const Grid3& g, int n_outer) { return ((g.M + C::B - 1) / C::B) * n_outer; }

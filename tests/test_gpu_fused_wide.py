@@ -1,4 +1,4 @@
-"""The fused y pass with one component per wave (few tiles, or FP64 at lengths 64 to 192),
+"""The fused y pass with one component per wave (few tiles, or FP64 at lengths 64 to 256),
 beside the other forms.
 
 Gates, as for every pass: one step against one oracle step (Def. 2.3 / Alg. 2) at 1e-12
@@ -20,12 +20,12 @@ pytestmark = pytest.mark.gpu
 TOL = {"fp64": 1e-12, "fp32": 2e-6}
 DOMAIN = (0.0, 2 * math.pi, -1.0, 4 * math.pi - 1.0, 0.5, 2.5)
 # (nx, ny, nz): every pencil length of the form; columns that do not fill a tile (M = 2, 3,
-# 12, 24 against tiles of 4 to 64); one tile only; several tiles a workgroup (FP64 128 and
-# 192 with more tiles than CUs); tile counts on both sides of the limits (32 x 32 x 512
+# 12, 24 against tiles of 4 to 64); one tile only; several tiles a workgroup (FP64 128,
+# 192 and 256 with more tiles than CUs); tile counts on both sides of the limits (32 x 32 x 512
 # has 512 tiles, 256 x 32 x 96 768; in FP32 96^3 has 576 and 128 x 96 x 96 768)
 SHAPES = [(48, 8, 128), (6, 12, 96), (96, 16, 64), (24, 24, 48), (32, 32, 512), (256, 32, 96), (4, 48, 64),
           (64, 64, 32), (96, 96, 96), (128, 96, 96), (128, 128, 48), (48, 192, 48), (96, 192, 96), (24, 256, 16),
-          (16, 512, 8)]
+          (48, 256, 64), (16, 512, 8)]
 
 
 def eifp():
