@@ -24,7 +24,12 @@ namespace eifp {
 
 template <typename T, class P>
 struct WideCfg {
-    static constexpr int N = P::N, CW = 64 / P::T, B = CW, NT = 6 * 64;
+    static constexpr int N = P::N, CW = 64 / P::T, B = CW;
+    // Waves of a workgroup: six, one per component; in FP32 at 128 and 256, whose two
+    // workgroups a CU keep the vector ALU busy, eight, so that they load the four SIMDs alike
+    // and take a tile's modes at once (fused pass, six waves / eight: 64x256x64 29.4 / 23.1 us,
+    // 64x128x256 43.5 / 36.8; at other lengths the registers spill or it makes no difference)
+    static constexpr int NW = sizeof(T) == 4 && N >= 128 && N % 3 != 0 ? 8 : 6, NT = NW * 64;
     // one empty row after every R0 positions (power of two) or every 4: the stores of the
     // first stage, R0 positions apart, then fall in different banks
     static constexpr int sk() {
@@ -70,7 +75,12 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
     const MemberDesc<T>& mem = md[blockIdx.z];
     const PropParams pp = mem.pp;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
-    const int q = wave, tc = lane % B, t = lane / B;
+    // with eight waves, two idle in the transforms: 0 and 1 or 2 and 3, by turns of the eight
+    // workgroups that go to the eight XCDs
+    const int idle = C::NW == 8 ? (((int)blockIdx.x >> 3) & 1) * 2 : 0;
+    const int qw = C::NW == 8 ? (wave < idle ? wave : wave - 2) : wave;
+    const bool fft = C::NW != 8 || wave < idle || wave >= idle + 2;
+    const int q = fft ? qw : 0, tc = lane % B, t = lane / B;
     const int G = (int)gridDim.x, ntiles = ntx * n_outer;
     const unsigned cbytes = (unsigned)cs * sizeof(cpx<T>);
     const unsigned sstep = (unsigned)(TT * pstride) * sizeof(cpx<T>);
@@ -83,7 +93,7 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
     };
     // the waves in the order in which they take the modes: with six waves on four SIMDs,
     // the two that share no SIMD with another come first
-    const int slot = (wave + 4) % 6 * 64 + lane;
+    const int slot = (C::NW == 8 ? wave : (wave + 4) % 6) * 64 + lane;
     TileCol<T, C> lds{s_x + q * PLANE + tc};
 
     double acc[Q];
@@ -93,14 +103,14 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
     bool active;
     unsigned voff = voff_of(w < ntiles ? w : 0, active);
     cpx<T> nv[E];
-    load_col<T, P>(nv, rs, voff, sstep);
+    if (fft) load_col<T, P>(nv, rs, voff, sstep);
     stage_table_plan<P>(s_tw, tw);
     __syncthreads();
     while (w < ntiles) {  // uniform over the workgroup
         const int wn = C::PERSIST ? persist_tile(k + 1, G) : ntiles;
         bool nactive = false;
         unsigned nvoff = 0;
-        {
+        if (fft) {
             cpx<T> v[E];
 #pragma unroll
             for (int i = 0; i < E; ++i) v[i] = nv[i];
@@ -177,7 +187,7 @@ k_fused_wide(const MemberDesc<T>* __restrict__ md, int M, int n_outer, int ntx, 
             }
         }
         __syncthreads();
-        if constexpr (MODE == Z_STEP || MODE == Z_JUMP) {
+        if constexpr (MODE == Z_STEP || MODE == Z_JUMP) if (fft) {
             cpx<T> v[E];
 #pragma unroll
             for (int i = 0; i < E; ++i) v[i] = lds.ld(t + TT * m_first<P>(i));

@@ -225,8 +225,8 @@ template <typename T, int N> struct WideSel {
     // us, other form / this one, FP64: 64^3 (256 tiles) 23.9 / 14.1, 64x32x256 (512) 23.7 /
     // 18.9, 256x32x256 (2048) 48.4 / 52.3, 256x64x256 (4096) 102 / 95, 128^3 55.2 / 43.5,
     // 192^3 248 / 179, 64x256x256 104 / 76, 256^3 419 / 376; FP32: 64^3
-    // 19.0 / 12.4, 96^3 (576) 30.3 / 28.1, 64x192x64 (512) 29.1 / 24.7, 64x64x256 (1024) 27.8
-    // / 31.1, 256^3 243 / 433.
+    // 19.0 / 12.4, 96^3 (576) 30.3 / 28.1, 64x256x64 (512) 30.2 / 22.7, 64x64x256 (1024) 26.6
+    // / 30.1, 64x128x256 (1024) 37.6 / 36.7, 256x96x256 (4096) 113 / 125, 256^3 248 / 306.
     static constexpr int max_tiles = N < 8 || N > 256 || C::lds_bytes > 160 * 1024 ? -1
                                      : sizeof(T) == 4                               ? 640
                                      : N >= 64                                      ? 0
