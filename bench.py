@@ -45,6 +45,10 @@ KERNEL_NAMES = {"x_fwd": "k_x_fwd", "z_fwd": "k_c2c", "y_fused": "k_fused", "z_i
                 "x_inv": "k_x_invfwd", "finalize": "k_finalize"}
 
 
+# the forms of the fused pass (at 256^3 k_fused_wide in FP64, k_fused in FP32)
+KERNEL_FORMS = {"k_fused": ("k_fused", "k_fused_wide", "k_fused_split")}
+
+
 def measured_traffic(prec: str, kernel: str):
     """HBM bytes per launch from the committed rocprofv3 counter summary, if it was taken
     on the current kernel sources; otherwise None."""
@@ -56,9 +60,10 @@ def measured_traffic(prec: str, kernel: str):
             rec = json.load(f)
         if rec.get("source_hash") != kernel_source_hash():
             return None
-        ent = rec["kernels"][prec][kernel]
+        ents = rec["kernels"][prec]
+        ent = next(ents[k] for k in KERNEL_FORMS.get(kernel, (kernel,)) if k in ents)
         return float(ent["fetch_bytes"]) + float(ent["write_bytes"])
-    except (KeyError, ValueError, TypeError):
+    except (KeyError, ValueError, TypeError, StopIteration):
         return None
 
 
@@ -81,7 +86,7 @@ def measured_valu(prec: str, kernel: str):
             return None
         ctype = "double" if prec == "fp64" else "float"
         for name, ent in rec["kernels"].items():
-            if name.startswith(f"{kernel}<{ctype},"):
+            if name.startswith(tuple(f"{k}<{ctype}," for k in KERNEL_FORMS.get(kernel, (kernel,)))):
                 return float(ent["raw"]["SQ_INSTS_VALU"])
     except (KeyError, ValueError, TypeError):
         return None
