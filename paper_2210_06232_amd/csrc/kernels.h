@@ -14,12 +14,16 @@
 //   y pass   fused: C2C along y for all six components of a tile, the mode-wise
 //            exponential propagator (Prop. 2.1/2.2, Alg. 2 step 4) with the 1/(Nx Ny Nz)
 //            of the inverse transform folded in, the invariant partial sums, and the
-//            inverse C2C along y.  Powers of two: one thread holds all six components
-//            (k_fused; persistent workgroups in FP64, components transformed in pairs);
-//            lengths with a factor 3: two thread groups hold H and E (k_fused_split).
+//            inverse C2C along y.  One component per wave (k_fused_wide, fused_wide.h) in
+//            FP64 at lengths 64 to 256 and elsewhere on grids of few tiles; otherwise
+//            one thread holds all six components (k_fused; persistent workgroups in
+//            FP64, components transformed in pairs) or, at lengths with a factor 3, two
+//            thread groups hold H and E (k_fused_split).
 //   z^-1, x^-1 as above in reverse (complex-to-real merge back).  Between two steps of
 //            one call, x^-1 and the next x pass are one kernel (k_x_invfwd) that keeps
-//            the physical row in registers: a call writes the state once, at its end.
+//            the physical row in registers: a call writes the state once, at its end.  Where
+//            the (x, z) plane of a component fits in LDS, the x and z passes between two
+//            fused passes are one kernel (k_xz, xz_plane.h).
 //
 // Every kernel works on a batch of solves of one shape ("members"): the member index
 // comes from the grid and selects a descriptor (buffers and per-solve scalars) from a

@@ -104,9 +104,10 @@ template <typename T, int N> struct ZCfg {
 #endif
 // values per thread in the split form for lengths with a factor 3: 12 in FP32, and in
 // FP64 from length 192 (a thread holds three components, so FP64 affords the plan with
-// fewer stages: 192 = 12 4 4 instead of 6 2 2 2 2 2, 4% off the 192^3 pass at one wave
-// per SIMD); shorter FP64 lengths keep 6 at two waves, since their few tiles would not
-// fill the device at one wave
+// fewer stages: 4% off a 192^3 pass at one wave per SIMD, before the one-component form
+// took that length; of the lengths that FP64 runs in this form 384 is the only one above
+// 48); shorter FP64 lengths keep 6 at two waves, since their few tiles would not fill the
+// device at one wave
 #ifndef EIFP_ZSE3_64
 #define EIFP_ZSE3_64 12
 #endif
@@ -203,13 +204,12 @@ int run_c2c(bool inv, int axis, const Grid3& g, const void* md, int nm, const vo
 }
 
 // Workgroups of the persistent fused pass (one partial record each; one per tile when
-// the precision's pass is not persistent): as many as the device holds at once (CUs times the step kernel's resident workgroups per CU), a
-// multiple of 8 when there are at least 8, at most one per tile.  The residency is
-// queried once per process; without a device (host-only use) every tile gets its own
-// workgroup.  Every mode uses the step kernel's count, so the partial buffers and the
-// finalize agree on it.
-// The fused pass's configuration for length N: the split form (k_fused_split) or the
-// six-components-per-thread form (k_fused), its tile width, threads and persistence.
+// the form is not persistent): as many as the device holds at once (CUs times the step
+// kernel's resident workgroups per CU), a multiple of 8 when there are at least 8, at
+// most one per tile.  The residency is queried once per process; without a device
+// (host-only use) every tile gets its own workgroup.  Every mode uses the step kernel's
+// count, so the partial buffers and the finalize agree on it.
+//
 // The one-component-per-wave form (k_fused_wide): values per thread, and where it is used.
 // 8 or 12 values up to length 64 (more waves for the few tiles of small grids), 16 or 12
 // above (one exchange less per transform at 128 and 256).
@@ -252,6 +252,8 @@ inline int resident_workgroups(const void* kernel, int threads) {
     }
     return cus * nb;
 }
+// The other forms for length N: the split form (k_fused_split) or the six-components-per-
+// thread form (k_fused), its tile width, threads and persistence.
 template <typename T, int N, int AXIS> struct FusedSel {
     static constexpr bool split = ZCfgS<T, N>::ok;
     static constexpr int B = split ? ZCfgS<T, N>::B : ZCfg<T, N>::B;

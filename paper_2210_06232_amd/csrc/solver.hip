@@ -4,12 +4,15 @@
 //   x forward (R2C split)  ->  z forward  ->  fused y (forward, propagator, invariant
 //   partials, inverse)  ->  z inverse (and the finalize of the invariant partials)  ->
 //   x inverse (C2R merge)
+// On grids whose (x, z) plane fits in LDS the x and z kernels on either side of the fused
+// pass are one (xz_plane.h), and a step in the middle of a call is two kernels.
 // The state stays in HBM in the ABI's own layout ([6][nz][ny][nx] reals); a step's
 // transforms run in the scratch buffer, and between consecutive steps of one call the
 // x inverse and the next x forward are one kernel.
 // A solver is a batch of one member: the kernels read its buffers and scalars from a
-// four-entry device descriptor array (0: step; 1: forward-only evaluation into the
-// scratch buffer; 2: forward transform into the anchor buffer; 3: jump from the anchor).
+// device descriptor array (D_STEP: step; D_FWD: forward-only evaluation into the scratch
+// buffer; D_ANCHOR: forward transform into the anchor buffer; D_JUMP: jump from the anchor),
+// each entry written by a kernel on the solver's stream.
 //
 // Jumps: the scheme is the exact flow of the Fourier semi-discretisation for any time
 // span (Def. 2.3; Alg. 2 takes t_end in one step), so the state after any number of
@@ -42,8 +45,8 @@ struct eifp_solver {
     bool anchor_valid = false;
     double t_anchor = 0.0;
     void* desc_dev = nullptr;    // DescImage[D_COUNT]
-    double desc_tau = 0.0;       // tau held by desc_dev[0]
-    double jump_span = 0.0;      // time span held by desc_dev[3]
+    double desc_tau = 0.0;       // tau held by desc_dev[D_STEP]
+    double jump_span = 0.0;      // time span held by desc_dev[D_JUMP]
     bool inv_current = false;    // inv_dev describes the current state
     double t = 0.0;
     long long steps = 0;

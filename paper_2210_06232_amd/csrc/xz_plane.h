@@ -9,7 +9,7 @@
 // separate passes, so the results are the same bits.
 //
 // Measured (one pass replacing z inverse + x inverse-forward + z forward, us): 32^3 FP64
-// 18 -> 9, 64^3 FP64 39 -> 16, 128^3 FP64 115 -> 51 (201 MB read and written: 3.9 TB/s,
+// 18 -> 9, 64^3 FP64 39 -> 15, 128^3 FP64 115 -> 51 (201 MB read and written: 3.9 TB/s,
 // against 6-7 for a copy of that size in the last-level cache), 96^3 FP32 39 -> 25.  What
 // bounds it: on small grids the latency of one load, two barriers and one store; on
 // 128^3 the LDS (about 15 movements of the plane, 24 us of the 51, a third of it bank
