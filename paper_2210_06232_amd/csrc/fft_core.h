@@ -502,19 +502,29 @@ struct LdsColsN {
     __device__ __forceinline__ void after_load() { cur ^= 1; }
 };
 
-// Rows: P pencils stored one after another with pitch LD (at least rows_pitch<T>(M)),
-// with one pad element after every 2^skew positions, so that positions a power of two
-// apart (the stride of the first exchange) spread over the banks.  Measured best: every
-// 8 in FP64, every 16 in FP32.
+// Rows: pencils stored one after another with pitch LD (rows_pitch<T, P>()), with one empty
+// element after every 2^skew positions, so that positions a power of two apart (the
+// stride of the first exchange) spread over the banks, and a pitch that is the smallest
+// odd multiple of the T threads a row has, so that the T consecutive positions that each
+// of the 64 / T rows of a wave reads at once fall side by side in the banks.  LDS cycles of
+// a wave's exchanges counted from the bank rules, against one empty element after 8 (FP64)
+// or 16 (FP32) positions and a pitch of one more than the row: FP64 length 96 1408 -> 1144,
+// 128 1024 -> 800, 256 1024 -> 832; FP32 128 644 -> 416, 192 1248 -> 768.  The LDS work of
+// a combined x kernel is only partly hidden behind its memory time: ten-step calls, us,
+// 192^3 FP64 5666 -> 5497, 256^3 FP64 13008 -> 12878 and FP32 6856 -> 6747, 512^3 FP32 (two
+// steps) 15251 -> 15070.
 #ifndef EIFP_XSKEW64
-#define EIFP_XSKEW64 3
+#define EIFP_XSKEW64 5
 #endif
 #ifndef EIFP_XSKEW32
 #define EIFP_XSKEW32 4
 #endif
 template <typename T> struct RowSkew { static constexpr int value = sizeof(T) == 8 ? EIFP_XSKEW64 : EIFP_XSKEW32; };
-template <typename T>
-__host__ __device__ constexpr int rows_pitch(int m) { return m + 1 + (RowSkew<T>::value ? m >> RowSkew<T>::value : 0); }
+template <typename T, class P>
+__host__ __device__ constexpr int rows_pitch() {
+    const int size = P::N + (RowSkew<T>::value ? (P::N - 1) >> RowSkew<T>::value : 0);
+    return (((size + P::T - 1) / P::T) | 1) * P::T;
+}
 // Ordering of LDS traffic that stays within one wave: a wave's LDS instructions are
 // performed in issue order, so a later read sees an earlier write of any lane of the
 // same wave once the compiler keeps them in program order (wavefront-scope fences and a

@@ -240,7 +240,7 @@ __device__ __forceinline__ void x_inverse_row(cpx<T> (&v)[P::E], int t, Lds& lds
 template <typename T, class P, int NP>
 __global__ void __launch_bounds__(P::T * NP)
 k_x_fwd(const MemberDesc<T>* __restrict__ md, long nrows, const cpx<T>* __restrict__ twx) {
-    constexpr int M = P::N, E = P::E, TT = P::T, LD = rows_pitch<T>(M);
+    constexpr int M = P::N, E = P::E, TT = P::T, LD = rows_pitch<T, P>();
     __shared__ T s_re[NP * LD];
     __shared__ T s_im[NP * LD];
     __shared__ cpx<T> s_tw[2 * M * TwParts<T>::value];
@@ -272,7 +272,7 @@ __device__ __forceinline__ long x_inv_row(long nrows, int np, int p) {
 template <typename T, class P, int NP>
 __device__ __forceinline__ void x_inv_body(const MemberDesc<T>* __restrict__ md, long nrows,
                                            const cpx<T>* __restrict__ twx) {
-    constexpr int M = P::N, E = P::E, TT = P::T, LD = rows_pitch<T>(M);
+    constexpr int M = P::N, E = P::E, TT = P::T, LD = rows_pitch<T, P>();
     __shared__ T s_re[NP * LD];
     __shared__ T s_im[NP * LD];
     __shared__ cpx<T> s_tw[2 * M * TwParts<T>::value];
@@ -311,7 +311,7 @@ k_x_inv(const MemberDesc<T>* __restrict__ md, long nrows, const cpx<T>* __restri
 template <typename T, class P, int NP>
 __device__ __forceinline__ void x_invfwd_body(const MemberDesc<T>* __restrict__ md, long nrows,
                                               const cpx<T>* __restrict__ twx) {
-    constexpr int M = P::N, E = P::E, TT = P::T, LD = rows_pitch<T>(M);
+    constexpr int M = P::N, E = P::E, TT = P::T, LD = rows_pitch<T, P>();
     __shared__ T s_re[NP * LD];
     __shared__ T s_im[NP * LD];
     __shared__ cpx<T> s_tw[2 * M * TwParts<T>::value];

@@ -35,14 +35,14 @@ constexpr int pow2floor(int a) {  // largest power of two <= a (a >= 1)
     return p;
 }
 
-// LDS budget of the x pass's row buffers per workgroup (rows of 2.3 KB in FP64 at
-// length 128: 21 rows, three workgroups per CU)
+// LDS budget of the x pass's row buffers per workgroup (rows of 2.2 KB in FP64 at
+// length 128: 22 rows, three workgroups per CU)
 #ifndef EIFP_XLDS_KB
 #define EIFP_XLDS_KB 48
 #endif
 template <typename T, int M> struct XCfg {
     using P = Plan<M, XYE<M>::E>;
-    static constexpr int NP = cmax(1, cmin(256 / P::T, (EIFP_XLDS_KB * 1024) / (rows_pitch<T>(M) * 2 * (int)sizeof(T))));
+    static constexpr int NP = cmax(1, cmin(256 / P::T, (EIFP_XLDS_KB * 1024) / (rows_pitch<T, P>() * 2 * (int)sizeof(T))));
 };
 
 // Row segment (bytes along x) of a tile of the single-component strided pass.
