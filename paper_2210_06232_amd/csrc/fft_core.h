@@ -565,17 +565,18 @@ __device__ __forceinline__ void stage_table(cpx<T>* dst, const cpx<T>* __restric
 
 // The stage-ordered table of plan P (N - 1 entries, then their lo parts at +N for FP32)
 // from the plain table src[k] = exp(-2 pi i k / N); the caller synchronises before use.
-template <class P, int s = 1, typename T>
+// SRC: stride of the length-N table in src, whose lo parts are at + SRC N.
+template <class P, int s = 1, int SRC = 1, typename T>
 __device__ __forceinline__ void stage_table_plan(cpx<T>* dst, const cpx<T>* __restrict__ src) {
     if constexpr (s < P::S) {
         constexpr int N = P::N, R = P::R[s], NS = span_before<P, s>(), off = NS - P::R[0];
         for (int i = threadIdx.x; i < NS * (R - 1); i += blockDim.x) {
             const int r = i / NS + 1, jm = i % NS;
-            const int k = jm * r * (N / (NS * R));
+            const int k = jm * r * (N / (NS * R)) * SRC;
             dst[off + i] = src[k];
-            if constexpr (TwParts<T>::value == 2) dst[N + off + i] = src[N + k];
+            if constexpr (TwParts<T>::value == 2) dst[N + off + i] = src[SRC * N + k];
         }
-        stage_table_plan<P, s + 1>(dst, src);
+        stage_table_plan<P, s + 1, SRC>(dst, src);
     }
 }
 

@@ -174,11 +174,14 @@ __device__ __forceinline__ void row_partners(const cpx<T> (&v)[P::E], cpx<T> (&w
 //   X[k] = (Z[k] + conj Z[M-k])/2 - (i/2) W^k (Z[k] - conj Z[M-k]),  W = exp(-2 pi i/Nx),
 // left in v at positions t + T m_last(i) (X[0] + i X[M] in slot 0).  The row's LDS and the
 // twiddle table are ordered by the caller (the table staged behind a block barrier).
-template <typename T, class P, class Lds>
+// HALF: s_tw holds the first M entries only (those the split reads) and, after them and
+// their lo parts, the transform's factors in stage order (stage_row_tables).
+template <typename T, class P, bool HALF = false, class Lds>
 __device__ __forceinline__ void x_forward_row(cpx<T> (&v)[P::E], int t, Lds& lds, const cpx<T>* s_tw) {
-    constexpr int M = P::N, E = P::E, TT = P::T;
+    constexpr int M = P::N, E = P::E, TT = P::T, LO = HALF ? M : 2 * M;
     static_assert(64 % TT == 0, "a row within one wave");
-    fft_pencil<P, false, 2>(v, t, lds, s_tw);
+    if constexpr (HALF) fft_pencil<P, false, kStagedTw>(v, t, lds, s_tw + M * TwParts<T>::value);
+    else fft_pencil<P, false, 2>(v, t, lds, s_tw);
     constexpr bool kRegs = row_partners_ok<P>();
     cpx<T> w[E];
     if constexpr (kRegs) {
@@ -199,7 +202,7 @@ __device__ __forceinline__ void x_forward_row(cpx<T> (&v)[P::E], int t, Lds& lds
             const cpx<T> zc = conj(kRegs ? w[i] : lds.ld(M - k));
             const cpx<T> ev = scale(z + zc, (T)0.5);
             const cpx<T> od = scale(mulmi(z - zc), (T)0.5);  // (Z - conj Z')/(2i)
-            v[i] = ev + twmul<false>(s_tw, k, 2 * M, od);
+            v[i] = ev + twmul<false>(s_tw, k, LO, od);
         }
     }
 }
@@ -208,9 +211,9 @@ __device__ __forceinline__ void x_forward_row(cpx<T> (&v)[P::E], int t, Lds& lds
 // merge Z[k] = (X[k] + conj X[M-k]) + i W^-k (X[k] - conj X[M-k]) (Z[0] from X[0], X[M]),
 // then the inverse length-M FFT: v ends at positions t + T m_last(i) (the row's reals in
 // pairs, unscaled).  STAGED: the row's LDS already holds the half spectrum.
-template <typename T, class P, bool STAGED = false, class Lds>
+template <typename T, class P, bool STAGED = false, bool HALF = false, class Lds>
 __device__ __forceinline__ void x_inverse_row(cpx<T> (&v)[P::E], int t, Lds& lds, const cpx<T>* s_tw) {
-    constexpr int M = P::N, E = P::E, TT = P::T;
+    constexpr int M = P::N, E = P::E, TT = P::T, LO = HALF ? M : 2 * M;
     static_assert(64 % TT == 0, "a row within one wave");
     constexpr bool kRegs = row_partners_ok<P>();
     cpx<T> w[E];
@@ -229,11 +232,33 @@ __device__ __forceinline__ void x_inverse_row(cpx<T> (&v)[P::E], int t, Lds& lds
             v[i] = {x.x + x.y, x.x - x.y};
         } else {
             const cpx<T> xc = conj(kRegs ? w[i] : lds.ld(M - k));
-            v[i] = (x + xc) + muli(twmul<true>(s_tw, k, 2 * M, x - xc));
+            v[i] = (x + xc) + muli(twmul<true>(s_tw, k, LO, x - xc));
         }
     }
     if constexpr (!kRegs || STAGED) lds.after_load();
-    fft_pencil<P, true, 2>(v, t, lds, s_tw);
+    if constexpr (HALF) fft_pencil<P, true, kStagedTw>(v, t, lds, s_tw + M * TwParts<T>::value);
+    else fft_pencil<P, true, 2>(v, t, lds, s_tw);
+}
+
+// The tables of a row kernel, from twx (exp(-2 pi i k / 2M), k < 2M, then the lo parts).  In
+// FP32 the first M entries for the split and the transform's factors in stage order,
+// together as large as twx itself: the lanes of a factor read then take consecutive
+// entries, hi and lo, instead of entries a power of two apart (ten-step call of 256^3 6738
+// -> 6703 us, two steps of 512^3 15011 -> 14869).  In FP64, one read a factor, it made no
+// difference at 256^3 and 192^3 slower (5486 -> 5540), so twx is kept as it is.
+template <typename T> constexpr bool kRowStaged = sizeof(T) == 4;
+template <class P, typename T>
+__device__ __forceinline__ void stage_row_tables(cpx<T>* s_tw, const cpx<T>* __restrict__ twx) {
+    constexpr int M = P::N;
+    if constexpr (kRowStaged<T>) {
+        for (int i = threadIdx.x; i < M; i += blockDim.x) {
+            s_tw[i] = twx[i];
+            s_tw[M + i] = twx[2 * M + i];
+        }
+        stage_table_plan<P, 1, 2>(s_tw + 2 * M, twx);
+    } else {
+        stage_table(s_tw, twx, 2 * M);
+    }
 }
 
 // Grid: (row blocks, members).  Forward reads state, writes work.
@@ -244,7 +269,7 @@ k_x_fwd(const MemberDesc<T>* __restrict__ md, long nrows, const cpx<T>* __restri
     __shared__ T s_re[NP * LD];
     __shared__ T s_im[NP * LD];
     __shared__ cpx<T> s_tw[2 * M * TwParts<T>::value];
-    stage_table(s_tw, twx, 2 * M);
+    stage_row_tables<P>(s_tw, twx);
     __syncthreads();  // the table, before any wave's first use
     const cpx<T>* src = md[blockIdx.y].state;
     cpx<T>* dst = md[blockIdx.y].work;
@@ -257,7 +282,7 @@ k_x_fwd(const MemberDesc<T>* __restrict__ md, long nrows, const cpx<T>* __restri
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = in[t + TT * m_first<P>(i)];
     LdsRows<T, LD> lds{s_re, s_im, p};
-    x_forward_row<T, P>(v, t, lds, s_tw);
+    x_forward_row<T, P, kRowStaged<T>>(v, t, lds, s_tw);
     store_row<T, P, true>(dst + row * M, v, t, active);
 }
 
@@ -276,7 +301,7 @@ __device__ __forceinline__ void x_inv_body(const MemberDesc<T>* __restrict__ md,
     __shared__ T s_re[NP * LD];
     __shared__ T s_im[NP * LD];
     __shared__ cpx<T> s_tw[2 * M * TwParts<T>::value];
-    stage_table(s_tw, twx, 2 * M);
+    stage_row_tables<P>(s_tw, twx);
     __syncthreads();  // the table, before any wave's first use
     const cpx<T>* src = md[blockIdx.y].work;
     cpx<T>* dst = md[blockIdx.y].state;
@@ -288,7 +313,7 @@ __device__ __forceinline__ void x_inv_body(const MemberDesc<T>* __restrict__ md,
     cpx<T> v[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = in[t + TT * m_first<P>(i)];
-    x_inverse_row<T, P>(v, t, lds, s_tw);
+    x_inverse_row<T, P, false, kRowStaged<T>>(v, t, lds, s_tw);
     store_row<T, P, true>(dst + row * M, v, t, active);
 }
 template <typename T, class P, int NP>
@@ -315,7 +340,7 @@ __device__ __forceinline__ void x_invfwd_body(const MemberDesc<T>* __restrict__ 
     __shared__ T s_re[NP * LD];
     __shared__ T s_im[NP * LD];
     __shared__ cpx<T> s_tw[2 * M * TwParts<T>::value];
-    stage_table(s_tw, twx, 2 * M);
+    stage_row_tables<P>(s_tw, twx);
     __syncthreads();  // the table, before any wave's first use
     cpx<T>* work = md[blockIdx.y].work;
     const int t = threadIdx.x % TT, p = threadIdx.x / TT;
@@ -326,7 +351,7 @@ __device__ __forceinline__ void x_invfwd_body(const MemberDesc<T>* __restrict__ 
     cpx<T> v[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = in[t + TT * m_first<P>(i)];
-    x_inverse_row<T, P>(v, t, lds, s_tw);
+    x_inverse_row<T, P, false, kRowStaged<T>>(v, t, lds, s_tw);
     // the physical row as materialised values of T, as a store and a reload would give
     // them: the empty asm keeps the compiler from merging the inverse's last operations
     // with the forward's first ones (without it, FP64 rows differ in the last bit from
@@ -334,7 +359,7 @@ __device__ __forceinline__ void x_invfwd_body(const MemberDesc<T>* __restrict__ 
 #pragma unroll
     for (int i = 0; i < E; ++i) asm volatile("" : "+v"(v[i].x), "+v"(v[i].y));
     last_to_first<P>(v);
-    x_forward_row<T, P>(v, t, lds, s_tw);
+    x_forward_row<T, P, kRowStaged<T>>(v, t, lds, s_tw);
     store_row<T, P, true>(work + row * M, v, t, active);
 }
 template <typename T, class P, int NP>
