@@ -115,7 +115,9 @@ eifp_status eifp_init(eifp_solver **out, int nx, int ny, int nz, const eifp_doma
  * (with the same rounding as separate calls: n steps in one call and n calls of one step
  * give the same bits) but not stored, and after a DEVICE error the fields and invariants
  * are undefined.  nsteps = 0 is a no-op.  Errors: INVALID_ARG (NULL solver, non-finite
- * tau, nsteps < 0), DEVICE. */
+ * tau, nsteps < 0), DEVICE (also where the stream is capturing a graph and tau is not the
+ * tau of the step before: a change of tau, like a change of a jump's time span or the
+ * first anchor, cannot be recorded). */
 eifp_status eifp_step(eifp_solver *s, double tau, long long nsteps);
 
 /* Anchor: store the spectrum of the current state (its forward 3-D transform, Def. 2.3

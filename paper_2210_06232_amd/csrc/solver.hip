@@ -79,7 +79,7 @@ eifp_status alloc(void** p, size_t n, long long* bytes) {
 }
 
 // Write one descriptor, in stream order: the image travels as the kernel's argument, so
-// nothing waits for the work before it (a copy from desc_host would have to; a jump of 64 x
+// nothing waits for the work before it (a copy from host memory would have to; a jump of 64 x
 // 128 x 256 FP32, whose span changes with every call, 111 -> 101 us with the fields and
 // invariants read out).
 __global__ void k_write_desc(DescImage d, DescImage* __restrict__ out) {
@@ -88,9 +88,22 @@ __global__ void k_write_desc(DescImage d, DescImage* __restrict__ out) {
 
 enum { D_STEP = 0, D_FWD = 1, D_ANCHOR = 2, D_JUMP = 3, D_COUNT = 4 };
 
+// A write recorded into a graph would run at a replay and not now, while the calls after
+// this one go by the span it holds (desc_tau, jump_span): a capturing stream is refused.
+// (The calls that write no descriptor, such as a step with the tau of the step before it,
+// can be captured.)
+eifp_status refuse_capture(const eifp_solver* s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    EIFP_HIP_TRY(hipStreamIsCapturing(s->stream, &cs));
+    if (cs == hipStreamCaptureStatusNone) return EIFP_OK;
+    return fail(EIFP_ERR_DEVICE, "the solver's stream is capturing: a new tau, time span or anchor cannot be recorded");
+}
+
 // Descriptor i, for a time span of `span` (the step size, or what a jump covers).  Steps
 // transform in the scratch buffer, so the state is written by a call's last step only.
 eifp_status write_desc(eifp_solver* s, int i, double span) {
+    const eifp_status st = refuse_capture(s);
+    if (st) return st;
     const Grid3& g = s->en.g;
     void* work = i == D_ANCHOR ? s->anchor : (i == D_JUMP ? s->state : s->scratch);
     const DescImage d{s->state, work, s->partials, s->inv_dev, i == D_JUMP ? s->anchor : nullptr,
@@ -110,8 +123,14 @@ const void* fwd_desc(const eifp_solver* s) { return desc_at(s, D_FWD); }
 eifp_status make_anchor(eifp_solver* s) {
     eifp_status st;
     if (!s->anchor) {
-        if ((st = alloc(&s->anchor, s->en.state_bytes(), &s->bytes))) return st;
-        if ((st = write_desc(s, D_ANCHOR, 0.0)) || (st = write_desc(s, D_JUMP, 0.0))) return st;
+        if ((st = refuse_capture(s)) || (st = alloc(&s->anchor, s->en.state_bytes(), &s->bytes))) return st;
+        if ((st = write_desc(s, D_ANCHOR, 0.0)) || (st = write_desc(s, D_JUMP, 0.0))) {
+            // no buffer without its descriptors: the next call starts over
+            (void)hipFree(s->anchor);
+            s->anchor = nullptr;
+            s->bytes -= (long long)s->en.state_bytes();
+            return st;
+        }
     }
     if ((st = s->en.forward_spectrum(desc_at(s, D_ANCHOR), 1, s->stream))) return st;
     s->anchor_valid = true;
