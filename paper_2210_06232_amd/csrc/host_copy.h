@@ -1,5 +1,5 @@
 // host_copy.h -- checks, conversions and first touches of large host field arrays, split
-// over a few threads.
+// over a few threads, and the buffers that several callers' copies go through.
 //
 // A solve's fields cross the host's memory once on the way in and once out; on one core
 // that is bound by page faults and scalar code (a burst of twelve served solves, 288 MB
@@ -78,6 +78,43 @@ long long check_finite(const double* src, TO* dst, long long n) {
     });
     return first;
 }
+
+// At most N buffers, each allocated by the first call that finds none free and kept until
+// release().  take() waits for no other user: with all N out, or none to be had, it returns
+// null and the caller does without.
+template <int N>
+class BufferPool {
+    std::mutex mu_;
+    void* free_[N] = {};
+    int nfree_ = 0, made_ = 0;
+
+public:
+    template <class Alloc>
+    void* take(Alloc alloc) {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (nfree_ > 0) return free_[--nfree_];
+            if (made_ == N) return nullptr;
+            ++made_;
+        }
+        void* p = alloc();
+        if (!p) {
+            std::lock_guard<std::mutex> lk(mu_);
+            --made_;
+        }
+        return p;
+    }
+    void give(void* p) {
+        std::lock_guard<std::mutex> lk(mu_);
+        free_[nfree_++] = p;
+    }
+    // every buffer is back; the pool is empty again
+    template <class Free>
+    void release(Free f) {
+        while (nfree_ > 0) f(free_[--nfree_]);
+        made_ = 0;
+    }
+};
 
 // Whether the array's pages look mapped: 16 of them, spread over it (a mincore call each).
 inline bool looks_resident(const char* p, long long bytes) {

@@ -145,6 +145,11 @@ double pct(std::vector<double> v, double q) {
 
 }  // namespace
 
+// Staging buffers of a server's large field copies: as many callers as this copy through
+// pinned memory at once, further ones do without (four threads, each its own 128^3 FP64
+// result: 11.4 ms through four, 14.8 through one in turn, 12.1 without).
+constexpr int kStages = 4;
+
 struct eifp_server {
     long long budget = 0;
     int max_batch = 1;
@@ -171,10 +176,9 @@ struct eifp_server {
     double first_arrive = -1, last_done = 0;
     bool stop = false;
     std::thread th;
-    // pinned staging of eifp_server_fields (two halves), allocated by its first large copy
-    // and given back by eifp_server_destroy; one copy uses it at a time
-    std::mutex stage_mu;
-    char* stage = nullptr;
+    // pinned staging of eifp_server_fields (two halves each), one to a large copy while it
+    // lasts; given back by eifp_server_destroy
+    BufferPool<kStages> stages;
     // host-side fault injection for tests of failure isolation: with
     // EIFP_SERVER_FAULT_CHUNK=n in the environment when the server is created, its n-th
     // chunk (counted over all groups from 1) fails as a device error would, before
@@ -677,53 +681,68 @@ eifp_status validate_request(const eifp_request* rq) {
 
 namespace {
 
-constexpr long long kStageHalf = 16LL << 20, kStageFrom = 1LL << 20;  // bytes
+constexpr long long kStageHalf = 16LL << 20;  // bytes
+// Arrays from this size on go through staging memory; below, the copy itself is the shorter
+// part (FP64 64^3, 6 MB an array: 0.82 ms directly, 0.98 staged; FP32 64^3, 3 MB: 3.3 / 0.91).
+constexpr long long kStageFrom64 = 8LL << 20, kStageFrom32 = 1LL << 20;
 
-// n values of T on the device to doubles in host memory, exactly.  Large copies go through
-// pinned memory in pieces, each spread to the destination by several threads while the next
-// is on its way (128^3: FP32 20 -> 3.0 ms, FP64 11.8 -> 3.7 ms); small ones, or any when there is no pinned
-// memory to be had, directly.
+void* stage_alloc() {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocDefault) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+// n values of T on the device to doubles in host memory, exactly, through the pinned staging
+// memory in pieces, each spread to the destination by several threads while the next is on
+// its way (128^3: FP32 20 -> 3.0 ms, FP64 11.8 -> 3.7 ms).
 template <typename T>
-hipError_t copy_out(eifp_server* sv, const char* from, double* to, long long n, hipStream_t io) {
-    hipError_t e = hipSuccess;
-    if (n * (long long)sizeof(T) >= kStageFrom) {
-        std::lock_guard<std::mutex> lk(sv->stage_mu);
-        if (!sv->stage && hipHostMalloc((void**)&sv->stage, 2 * kStageHalf, hipHostMallocDefault) != hipSuccess) {
-            sv->stage = nullptr;
-            (void)hipGetLastError();
-        }
-        if (sv->stage) {
-            const long long per = kStageHalf / (long long)sizeof(T), np = (n + per - 1) / per;
-            auto piece = [&](long long c) {
-                const long long b = c * per, m = std::min(per, n - b);
-                return hipMemcpyAsync(sv->stage + (c & 1) * kStageHalf, from + b * (long long)sizeof(T),
-                                      m * (long long)sizeof(T), hipMemcpyDeviceToHost, io);
-            };
-            e = piece(0);
-            for (long long c = 0; c < np && e == hipSuccess; ++c) {
-                e = hipStreamSynchronize(io);
-                if (e == hipSuccess && c + 1 < np) e = piece(c + 1);
-                if (e != hipSuccess) break;
-                const T* f = (const T*)(sv->stage + (c & 1) * kStageHalf);
-                double* d = to + c * per;
-                host_ranges(std::min(per, n - c * per), 8, [=](long long b, long long end) {
-                    for (long long q = b; q < end; ++q) d[q] = (double)f[q];
-                });
-            }
-            (void)hipStreamSynchronize(io);  // nothing still writes the staging memory
-            return e;
-        }
+hipError_t copy_staged(char* stage, const T* from, double* to, long long n, hipStream_t io) {
+    const long long per = kStageHalf / (long long)sizeof(T), np = (n + per - 1) / per;
+    auto piece = [&](long long c) {
+        const long long b = c * per, m = std::min(per, n - b);
+        return hipMemcpyAsync(stage + (c & 1) * kStageHalf, from + b, m * (long long)sizeof(T), hipMemcpyDeviceToHost, io);
+    };
+    hipError_t e = piece(0);
+    for (long long c = 0; c < np && e == hipSuccess; ++c) {
+        e = hipStreamSynchronize(io);
+        if (e == hipSuccess && c + 1 < np) e = piece(c + 1);
+        if (e != hipSuccess) break;
+        const T* f = (const T*)(stage + (c & 1) * kStageHalf);
+        double* d = to + c * per;
+        host_ranges(std::min(per, n - c * per), 8, [=](long long b, long long end) {
+            for (long long q = b; q < end; ++q) d[q] = (double)f[q];
+        });
+    }
+    (void)hipStreamSynchronize(io);  // nothing still writes the staging memory
+    return e;
+}
+
+// The H and E arrays (n3 values each) of a state of T, as doubles, into host memory.
+template <typename T>
+hipError_t copy_out(eifp_server* sv, const T* from, double* H, double* E, long long n3, hipStream_t io) {
+    hipError_t e;
+    const bool large = n3 * (long long)sizeof(T) >= (sizeof(T) == 8 ? kStageFrom64 : kStageFrom32);
+    if (char* stage = large ? (char*)sv->stages.take(stage_alloc) : nullptr) {
+        e = copy_staged<T>(stage, from, H, n3, io);
+        if (e == hipSuccess) e = copy_staged<T>(stage, from + n3, E, n3, io);
+        sv->stages.give(stage);
+        return e;
     }
     if constexpr (sizeof(T) == 8) {
-        e = hipMemcpyAsync(to, from, n * 8, hipMemcpyDeviceToHost, io);
+        e = hipMemcpyAsync(H, from, n3 * 8, hipMemcpyDeviceToHost, io);
+        if (e == hipSuccess) e = hipMemcpyAsync(E, from + n3, n3 * 8, hipMemcpyDeviceToHost, io);
         return e == hipSuccess ? hipStreamSynchronize(io) : e;
     } else {
-        std::unique_ptr<T[]> tmp(new (std::nothrow) T[n]);
+        std::unique_ptr<T[]> tmp(new (std::nothrow) T[2 * n3]);
         if (!tmp) return hipErrorOutOfMemory;
-        e = hipMemcpyAsync(tmp.get(), from, n * (long long)sizeof(T), hipMemcpyDeviceToHost, io);
+        e = hipMemcpyAsync(tmp.get(), from, 2 * n3 * (long long)sizeof(T), hipMemcpyDeviceToHost, io);
         if (e == hipSuccess) e = hipStreamSynchronize(io);
         if (e == hipSuccess)
-            for (long long q = 0; q < n; ++q) to[q] = (double)tmp[q];
+            for (long long q = 0; q < n3; ++q) {
+                H[q] = (double)tmp[q];
+                E[q] = (double)tmp[n3 + q];
+            }
         return e;
     }
 }
@@ -873,12 +892,8 @@ eifp_status eifp_server_fields(eifp_server* sv, long long req_id, double* H, dou
     hipStream_t io = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&io, hipStreamNonBlocking);
     if (e == hipSuccess) {
-        const bool wide = r->rq.prec == EIFP_FP64;
-        for (int part = 0; part < 2 && e == hipSuccess; ++part) {
-            const char* from = (const char*)src + part * n3 * (wide ? 8 : 4);
-            double* to = part ? E : H;
-            e = wide ? copy_out<double>(sv, from, to, n3, io) : copy_out<float>(sv, from, to, n3, io);
-        }
+        e = r->rq.prec == EIFP_FP64 ? copy_out<double>(sv, (const double*)src, H, E, n3, io)
+                                    : copy_out<float>(sv, (const float*)src, H, E, n3, io);
         (void)hipStreamDestroy(io);
     }
     {
@@ -981,7 +996,7 @@ eifp_status eifp_server_destroy(eifp_server* sv) {
         sv->cv_ev.notify_all();
     }
     if (sv->th.joinable()) sv->th.join();
-    if (sv->stage) (void)hipHostFree(sv->stage);
+    sv->stages.release([](void* p) { (void)hipHostFree(p); });
     delete sv;
     return EIFP_OK;
 }
