@@ -94,6 +94,7 @@ struct Group {
     double* inv_host = nullptr;      // pinned
     long long bytes = 0;
     int nparts = 0;
+    int slots = 1;                   // members the batch tables hold
     std::vector<Req*> members;
     bool dirty = true;
     bool in_flight = false;
@@ -113,11 +114,11 @@ int nparts_of(const Key& k) {
     return k.prec == EIFP_FP64 ? partial_capacity<double>(g) : partial_capacity<float>(g);
 }
 
-long long group_bytes_of(const Key& k, int max_batch) {
+long long group_bytes_of(const Key& k, int slots) {
     const long long ts = k.prec == EIFP_FP64 ? 8 : 4;
     const long long np = nparts_of(k);
     // partial and invariant slots, two descriptor regions (jumps and anchoring), tables
-    return (long long)max_batch * (np * INV_NPART * 8 + 8 * 8 + 2 * (long long)sizeof(DescImage)) +
+    return (long long)slots * (np * INV_NPART * 8 + 8 * 8 + 2 * (long long)sizeof(DescImage)) +
            2 * ts * (k.nx + k.ny + k.nz);
 }
 
@@ -133,6 +134,16 @@ long long footprint_of(int nx, int ny, int nz, int prec, int flags) {
     const long long sb = state_bytes_of(nx, ny, nz, prec);
     return sb * (1 + ((flags & EIFP_REQ_NO_SNAPSHOT) ? 0 : 1) + ((flags & EIFP_REQ_ANCHORED) ? 1 : 0) +
                  (uses_work(sb, flags) ? 1 : 0));
+}
+
+// Members that a group of shape k can ever have: max_batch, or as many as fit the budget
+// if those are fewer.  The batch tables are sized for these: sized for max_batch, the
+// partial records of a large batch limit (64 bytes a fused workgroup and member) could take
+// more than the requests they are for, and shut out ones that fit.
+int slots_of(const Key& k, long long budget, int max_batch) {
+    const long long each =
+        footprint_of(k.nx, k.ny, k.nz, k.prec, EIFP_REQ_NO_SNAPSHOT | (k.anchored ? EIFP_REQ_ANCHORED : 0));
+    return (int)std::max(1LL, std::min<long long>(max_batch, budget / each));
 }
 
 double pct(std::vector<double> v, double q) {
@@ -205,21 +216,21 @@ void group_free(Group* g) {
     g->en.release();
 }
 
-eifp_status group_alloc(Group* g, int max_batch) {
+eifp_status group_alloc(Group* g) {
     EIFP_HIP_TRY(hipStreamCreateWithFlags(&g->st, hipStreamNonBlocking));
     EIFP_HIP_TRY(hipEventCreate(&g->ev0));
     EIFP_HIP_TRY(hipEventCreate(&g->ev1));
     eifp_status st = g->en.init(g->key.nx, g->key.ny, g->key.nz, (eifp_precision)g->key.prec, g->st);
     if (st) return st;
     g->nparts = g->en.nrec;
-    const size_t pb = (size_t)max_batch * g->nparts * INV_NPART * sizeof(double);
-    if (hipMalloc((void**)&g->partials, pb) != hipSuccess || hipMalloc((void**)&g->inv_dev, max_batch * 64) != hipSuccess ||
-        hipMalloc(&g->desc_dev, 2 * max_batch * sizeof(DescImage)) != hipSuccess) {
+    const size_t pb = (size_t)g->slots * g->nparts * INV_NPART * sizeof(double);
+    if (hipMalloc((void**)&g->partials, pb) != hipSuccess || hipMalloc((void**)&g->inv_dev, g->slots * 64) != hipSuccess ||
+        hipMalloc(&g->desc_dev, 2 * g->slots * sizeof(DescImage)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(EIFP_ERR_OUT_OF_MEMORY, "batch table allocation failed");
     }
-    EIFP_HIP_TRY(hipHostMalloc((void**)&g->desc_host, 2 * max_batch * sizeof(DescImage), hipHostMallocDefault));
-    EIFP_HIP_TRY(hipHostMalloc((void**)&g->inv_host, max_batch * 64, hipHostMallocDefault));
+    EIFP_HIP_TRY(hipHostMalloc((void**)&g->desc_host, 2 * g->slots * sizeof(DescImage), hipHostMallocDefault));
+    EIFP_HIP_TRY(hipHostMalloc((void**)&g->inv_host, g->slots * 64, hipHostMallocDefault));
     return EIFP_OK;
 }
 
@@ -359,10 +370,11 @@ Group* get_group(eifp_server* sv, const Key& k, eifp_status* st) {
     if (it != sv->groups.end()) return it->second.get();
     std::unique_ptr<Group> g(new Group);
     g->key = k;
-    g->bytes = group_bytes_of(k, sv->max_batch);
+    g->slots = slots_of(k, sv->budget, sv->max_batch);
+    g->bytes = group_bytes_of(k, g->slots);
     g->nparts = nparts_of(k);
     if (!sv->dry) {
-        *st = group_alloc(g.get(), sv->max_batch);
+        *st = group_alloc(g.get());
         if (*st) {
             group_free(g.get());
             return nullptr;
@@ -415,8 +427,8 @@ bool admit(eifp_server* sv) {
         auto git = sv->groups.find(k);
         Group* g = git == sv->groups.end() ? nullptr : git->second.get();
         const long long need = footprint_of(k.nx, k.ny, k.nz, k.prec, r->rq.flags) +
-                               (g ? 0 : group_bytes_of(k, sv->max_batch));
-        const bool slot = !g || (!g->in_flight && g->readers == 0 && (int)g->members.size() < sv->max_batch);
+                               (g ? 0 : group_bytes_of(k, slots_of(k, sv->budget, sv->max_batch)));
+        const bool slot = !g || (!g->in_flight && g->readers == 0 && (int)g->members.size() < g->slots);
         const bool fits = sv->used + need <= sv->budget;
         if (slot && fits) {
             eifp_status st = EIFP_OK;
@@ -465,7 +477,7 @@ eifp_status launch_jump_chunk(eifp_server* sv, Group* g) {
         for (Req* r : g->members)
             if (!r->anchored) {
                 const PropParams p0 = make_params(gg.nx, gg.ny, gg.nz, r->rq.dom, r->rq.mu, r->rq.eps, 0.0);
-                g->desc_host[sv->max_batch + na++] = DescImage{r->state, r->spec, nullptr, nullptr, nullptr, p0};
+                g->desc_host[g->slots + na++] = DescImage{r->state, r->spec, nullptr, nullptr, nullptr, p0};
             }
         for (int i = 0; i < nm; ++i) {
             Req* r = g->members[i];
@@ -474,11 +486,11 @@ eifp_status launch_jump_chunk(eifp_server* sv, Group* g) {
                                         g->inv_dev + (size_t)i * 8, r->spec,
                                         make_params(gg.nx, gg.ny, gg.nz, r->rq.dom, r->rq.mu, r->rq.eps, span)};
         }
-        EIFP_HIP_TRY(hipMemcpyAsync(g->desc_dev, g->desc_host, (size_t)(sv->max_batch + na) * sizeof(DescImage),
+        EIFP_HIP_TRY(hipMemcpyAsync(g->desc_dev, g->desc_host, (size_t)(g->slots + na) * sizeof(DescImage),
                                     hipMemcpyHostToDevice, g->st));
         EIFP_HIP_TRY(hipEventRecord(g->ev0, g->st));
         eifp_status st;
-        if (na && (st = g->en.forward_spectrum((const char*)g->desc_dev + sv->max_batch * sizeof(DescImage), na, g->st)))
+        if (na && (st = g->en.forward_spectrum((const char*)g->desc_dev + g->slots * sizeof(DescImage), na, g->st)))
             return st;
         if ((st = g->en.jump(g->desc_dev, nm, g->st, true))) return st;
         for (Req* r : g->members)
@@ -792,7 +804,8 @@ eifp_status eifp_server_submit(eifp_server* sv, const eifp_request* rq, long lon
     eifp_status st = validate_request(rq);
     if (st) return st;
     const Key k = key_of(*rq);
-    const long long need = footprint_of(k.nx, k.ny, k.nz, k.prec, rq->flags) + group_bytes_of(k, sv->max_batch);
+    const long long need = footprint_of(k.nx, k.ny, k.nz, k.prec, rq->flags) +
+                           group_bytes_of(k, slots_of(k, sv->budget, sv->max_batch));
     if (need > sv->budget)
         return fail(EIFP_ERR_OUT_OF_MEMORY, "request needs %lld bytes, budget is %lld", need, sv->budget);
     const long long n3 = 3LL * rq->nx * rq->ny * rq->nz;
