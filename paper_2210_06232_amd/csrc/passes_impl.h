@@ -227,9 +227,13 @@ template <typename T, int N> struct WideSel {
     // 192^3 248 / 179, 64x256x256 104 / 76, 256^3 419 / 376; FP32: 64^3
     // 19.0 / 12.4, 96^3 (576) 30.3 / 28.1, 64x256x64 (512) 30.2 / 22.7, 64x64x256 (1024) 26.6
     // / 30.1, 64x128x256 (1024) 37.6 / 36.7, 256x96x256 (4096) 113 / 125, 256^3 248 / 306.
+    // FP64 at 12 and 24 wins up to 256 tiles, one workgroup a CU, and loses beyond (us a
+    // step, other form / this one: 64x24x256 (256) 42.6 / 38.7, 8x24x256 (256) 28.5 / 26.6,
+    // 8x24x384 (384) 38.3 / 40.3, 256x24x96 (384) 59.9 / 62.7, 256x12x256 (512) 71.6 / 74.2).
     static constexpr int max_tiles = N < 8 || N > 256 || C::lds_bytes > 160 * 1024 ? -1
                                      : sizeof(T) == 4                               ? 640
                                      : N >= 64                                      ? 0
+                                     : N == 12 || N == 24                           ? 256
                                                                                     : 512;
     static constexpr bool compiled = max_tiles >= 0, always = max_tiles == 0;
     static int tiles(const Grid3& g, int n_outer) { return ((g.M + C::B - 1) / C::B) * n_outer; }
