@@ -560,9 +560,27 @@ int xz_dispatch(bool launch, int kind, const Grid3& g, const void* md, int nm, c
             return kUnsupported;
     }
 }
+// The pass is the faster one nearly wherever it is compiled, but not for the largest or
+// longest FP64 planes, one a CU and each a long serial chain, when there are few of them: the
+// separate passes then spread over more CUs.  Planes beyond 8192 points (9216: the lengths
+// with a factor 3) lose below 72 planes, and again just above one a CU, where a second
+// round runs for a few of them (us a step in long calls, separate / plane pass: 192x4x96
+// 28.4 / 37.9, 96x6x192 32.3 / 36.0, 192x8x96 36.3 / 41.1, 192x12x96 44.6 / 45.4, 192x16x96 59.6 /
+// 54.1; single steps at Ny = 48, 288 planes: 192x48x96 111.5 / 117.5, 48x48x384 117.2 / 123.0).
+// Columns of 384 and 512 lose below 48 planes from M = 12 in single steps, which the long
+// calls make up for in part (single steps, then long calls: 32x4x384 43.1 / 47.6 and 27.0 /
+// 28.2, 32x6x512 52.8 / 56.7 and 35.4 / 33.6, 24x4x512 43.7 / 45.7 and 27.9 / 26.1; from 48
+// planes 32x8x512 55.7 / 55.3 and 37.6 / 33.1).
+template <typename T>
+bool xz_pays(const Grid3& g) {
+    if (sizeof(T) == 4) return true;
+    const int planes = 6 * g.ny;
+    if (g.M * g.nz > 8192) return planes >= 72 && (planes <= 256 || planes > 288);
+    return planes >= 48 || g.nz < 384 || g.M < 12;
+}
 template <typename T>
 bool xz_ok(const Grid3& g) {
-    return xz_dispatch<T>(false, 0, g, nullptr, 1, nullptr, nullptr, nullptr, 0) == kOk;
+    return xz_dispatch<T>(false, 0, g, nullptr, 1, nullptr, nullptr, nullptr, 0) == kOk && xz_pays<T>(g);
 }
 template <typename T>
 int launch_xz(int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz, hipStream_t st,
