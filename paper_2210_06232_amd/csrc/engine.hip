@@ -46,17 +46,34 @@ bool use_xz(const Engine& en) {
     return xz_ok<T>(en.g);
 }
 
-// Of the others (Nx below 16 or Nz below 8, or a plane too large), those whose (y, z) plane
-// of all six components fits in LDS step with the plane pass in place of the z forward,
-// fused y and z inverse passes (the partial records it writes, one per packed x column,
-// must fit the member's partials buffer, which every caller sizes for partial_capacity
-// records); the x kernel after it finalizes.  Where both are compiled the (x, z) plane is
-// faster, having Ny times six workgroups instead of Nx/2 (us per FP64 step, (y, z) / (x, z)
-// plane: 16^3 13.6 / 12.0, 32x16x16 16.3 / 12.6, 24^3 23.8 / 14.6, 256x24x24 34.8 / 24.1);
-// without the latter a (y, z) plane beats the separate passes (8^3 10.1 / 19.0).
+// Where both planes are compiled, whether a step takes the (y, z) plane all the same.  The
+// (x, z) plane is faster as a rule, having Ny times six workgroups instead of Nx/2 (us per FP64
+// step, (y, z) / (x, z) plane: 16^3 13.6 / 12.0, 32x16x16 16.3 / 12.6, 24^3 23.8 / 14.6, 256x24x24
+// 34.8 / 24.1), but with few y the (y, z) plane, one launch for the z, y and z work, is ahead
+//   - of (x, z) planes of 4608 points or more (FP64 384x4x32 22.9 / 25.5, 512x4x32 22.8 / 26.2,
+//     384x6x24 22.5 / 24.1; FP32 384x4x32 19.4 / 23.2; at Ny = 8 equal: FP64 384x8x24 23.9 / 23.7),
+//   - on the smallest (y, z) planes:
+//     M = 8 and 12, in FP32 up to 144 points (16x6x8 9.7 / 11.8, 24x6x12 10.6 / 12.6, 16x12x8
+//     10.1 / 11.6; but 16x4x24 loses, 16x16x8 is equal), in FP64 up to 72 (16x6x8 10.5 / 11.1),
+//     and in FP32 the other lengths with a factor 3 from Ny = 6 to 72 points (96x6x8 11.9 /
+//     13.1, 48x6x12 12.4 / 13.2; but 64x6x8 12.7 / 11.9).
+template <typename T>
+bool yz_first(const Grid3& g) {
+    const int points = g.ny * g.nz;
+    if (g.M * g.nz >= 4608) return g.ny <= 6;
+    if (sizeof(T) == 8) return g.M <= 12 && g.ny >= 6 && points <= 72;
+    return g.M <= 12 ? points <= 144 && g.nz <= 4 * g.ny : g.M % 3 == 0 && g.ny >= 6 && points <= 72;
+}
+
+// Grids whose (y, z) plane of all six components fits in LDS step with the plane pass in
+// place of the z forward, fused y and z inverse passes where the (x, z) plane pass does not
+// take them (Nx below 16 or Nz below 8, and yz_first); the partial records it writes, one
+// per packed x column, must fit the member's partials buffer, which every caller sizes for
+// partial_capacity records; the x kernel after it finalizes.  Against the separate passes:
+// 8^3 10.1 / 19.0 us.
 template <typename T>
 bool use_plane(const Engine& en) {
-    return plane_ok<T>(en.g) && !use_xz<T>(en) && en.g.M <= en.nrec;
+    return plane_ok<T>(en.g) && (!use_xz<T>(en) || yz_first<T>(en.g)) && en.g.M <= en.nrec;
 }
 
 }  // namespace
@@ -112,7 +129,7 @@ template <typename T>
 eifp_status run_steps(const Engine& en, const void* md, int nm, long long nsteps, hipStream_t st, hipEvent_t* ev,
                       long long inv_from) {
     int rc;
-    const bool xz = use_xz<T>(en), plane = use_plane<T>(en);
+    const bool plane = use_plane<T>(en), xz = !plane && use_xz<T>(en);
     for (long long n = 0; n < nsteps; ++n) {
         const bool want_inv = n >= inv_from;
         hipEvent_t* e = ev ? ev + 7 * n : nullptr;
