@@ -1,0 +1,30 @@
+"""The energy that FP64 steps gain from the transforms' rounded constants, on planes whose
+lengths 32 and 64 can be transformed in several ways: the plans differ in how many values
+meet sqrt(2)/2, whose rounded value is 6.8e-17 too large relatively.
+
+Gates, relative energy a step over 400 steps, halfway between what the separate passes'
+plans give on these fields (2.3e-16, 2.1e-16, 1.7e-16, 1.0e-16) and what (8, 8) and (8, 4) gave
+(3.4e-16, 2.6e-16, 2.9e-16, 2.2e-16)."""
+import math
+
+import pytest
+
+from paper_2210_06232_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+CUBE = (0.0, 2 * math.pi, 0.0, 2 * math.pi, 0.0, 2 * math.pi)
+
+
+@pytest.mark.parametrize("shape,gate", [((64, 64, 64), 2.85e-16), ((32, 32, 64), 2.35e-16), ((64, 32, 64), 2.3e-16),
+                                        ((128, 32, 32), 1.6e-16)], ids=lambda v: str(v).replace(", ", "x"))
+def test_energy_gain_per_step(shape, gate):
+    from paper_2210_06232_amd import eifp as m
+    H, E = inputs.random_fields(shape, CUBE, workload=71, p=2.0)
+    n = 400
+    with m.Solver(H, E, CUBE, 1.0, 1.0, "fp64") as s:
+        before = s.invariants()["energy"]
+        s.step(0.1, n)
+        gain = (s.invariants()["energy"] / before - 1.0) / n
+    print(f"{shape}: {gain:.3e} a step")
+    assert abs(gain) <= gate
