@@ -43,10 +43,13 @@ PASSES = ("x_fwd", "z_fwd", "y_fused", "z_inv", "x_inv", "finalize")
 # the x-inverse slot holds the combined x kernel (every step but the last) and one k_x_inv
 KERNEL_NAMES = {"x_fwd": "k_x_fwd", "z_fwd": "k_c2c", "y_fused": "k_fused", "z_inv": "k_c2c",
                 "x_inv": "k_x_invfwd", "finalize": "k_finalize"}
-
-
-# the forms of the fused pass (at 256^3 k_fused_wide in FP64, k_fused in FP32)
+# the forms of the fused pass, and the one that runs at 256^3
 KERNEL_FORMS = {"k_fused": ("k_fused", "k_fused_wide", "k_fused_split")}
+FUSED_FORM = {"fp64": "k_fused_wide", "fp32": "k_fused"}
+
+
+def kernel_name(prec: str, slot: str) -> str:
+    return FUSED_FORM[prec] if slot == "y_fused" else KERNEL_NAMES[slot]
 
 
 def measured_traffic(prec: str, kernel: str):
@@ -168,7 +171,7 @@ def summarize(prec: str, steps: int, wall: float, pass_ms: dict, inv: dict):
     traffic = measured_traffic(prec, KERNEL_NAMES[dominant])
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": traffic,
-                "kernel": KERNEL_NAMES[dominant], "pass": dominant,
+                "kernel": kernel_name(prec, dominant), "pass": dominant,
                 "alg_bytes_per_launch": alg_bytes, "avg_launch_ms": round(avg_ms, 5)}
     # the same launch against the vector-ALU issue ceiling (instructions per launch from
     # the committed SQ counters of the same kernel sources)
@@ -178,7 +181,7 @@ def summarize(prec: str, steps: int, wall: float, pass_ms: dict, inv: dict):
         gips = valu / (avg_ms * 1e-3) / 1e9
         issue = {"bound": "alu", "achieved": round(gips, 1), "peak": PEAK_VALU_GIPS,
                  "unit": "G VALU wave-instructions/s", "frac": round(gips / PEAK_VALU_GIPS, 4),
-                 "kernel": KERNEL_NAMES[dominant], "valu_per_launch": valu}
+                 "kernel": kernel_name(prec, dominant), "valu_per_launch": valu}
     step_bytes = sum(slot_bytes.values())
     value = ns / (ms_per_step * 1e-3)
     # the step's HBM bytes as the counters count them (committed summary of the same
