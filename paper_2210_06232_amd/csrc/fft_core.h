@@ -236,7 +236,6 @@ EIFP_PLAN(48, 6, 6, 2, 2, 2)
 EIFP_PLAN(64, 16, 16, 4)
 EIFP_PLAN(64, 8, 8, 8)
 EIFP_PLAN(96, 12, 12, 4, 2)
-EIFP_PLAN(96, 6, 6, 2, 2, 2, 2)
 EIFP_PLAN(128, 16, 16, 8)
 EIFP_PLAN(128, 8, 8, 8, 2)
 EIFP_PLAN(192, 12, 12, 4, 4)
@@ -245,14 +244,14 @@ EIFP_PLAN(256, 8, 8, 8, 4)
 EIFP_PLAN(384, 12, 12, 4, 4, 2)
 EIFP_PLAN(512, 16, 16, 16, 2)
 EIFP_PLAN(512, 8, 8, 8, 8)
-// four and six values per thread (low register pressure, for the six-component z pass in FP64)
+// fewer values per thread: 32 and 64 at four (with 16 above) for small FP64 planes of the (x, z)
+// plane pass, the rest for tuning builds of the fused pass
 EIFP_PLAN(8, 4, 4, 2)
 EIFP_PLAN(32, 4, 4, 4, 2)
 EIFP_PLAN(64, 4, 4, 4, 4)
 EIFP_PLAN(128, 4, 4, 4, 4, 2)
 EIFP_PLAN(256, 4, 4, 4, 4, 4)
 EIFP_PLAN(512, 4, 4, 4, 4, 4, 2)
-EIFP_PLAN(192, 6, 6, 2, 2, 2, 2, 2)
 EIFP_PLAN(384, 6, 6, 2, 2, 2, 2, 2, 2)
 #undef EIFP_PLAN
 

@@ -322,8 +322,9 @@ k_x_inv(const MemberDesc<T>* __restrict__ md, long nrows, const cpx<T>* __restri
     x_inv_body<T, P, NP>(md, nrows, twx);
 }
 
-// Between two steps (work != state): the x inverse of one step and the x forward of the
-// next on the same row, in place on work (the spectrum after the z inverse).  The
+// Between two steps: the x inverse of one step and the x forward of the next on the same
+// row, in place on work (the spectrum after the z inverse); the state buffer is not
+// touched, so work may be state.  The
 // physical row, the state after this step, lives only in registers: within one call
 // nothing reads an intermediate state (the invariants are summed in spectral space by
 // the fused pass), and the call's last step ends with k_x_inv, which writes the state.

@@ -29,8 +29,8 @@ struct Grid3 {
     long cs() const { return (long)nz * ny * M; }  // complex elements per component
 };
 
-// x pass: X_FWD (state -> work), X_INV (work -> state), or X_INVFWD (between two steps
-// with work != state: the inverse and the next step's forward, in place on work)
+// x pass: X_FWD (state -> work), X_INV (work -> state), or X_INVFWD (between two steps: the
+// inverse and the next step's forward, in place on work, so work may be state)
 enum XKind { X_FWD = 0, X_INV = 1, X_INVFWD = 2 };
 // fin_nparts > 0 (X_INV and X_INVFWD only): one extra workgroup per member also
 // finalizes that many invariant partial records (those of a preceding plane pass)

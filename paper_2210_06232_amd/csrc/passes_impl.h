@@ -230,6 +230,12 @@ template <typename T, int N> struct WideSel {
     // FP64 at 12 and 24 wins up to 256 tiles, one workgroup a CU, and loses beyond (us a
     // step, other form / this one: 64x24x256 (256) 42.6 / 38.7, 8x24x256 (256) 28.5 / 26.6,
     // 8x24x384 (384) 38.3 / 40.3, 256x24x96 (384) 59.9 / 62.7, 256x12x256 (512) 71.6 / 74.2).
+    // The count is one member's, whatever the batch: the forms differ in plans and in the
+    // order of their sums, and a batched solve gives the bits of a solve alone.  On batches
+    // of many small solves that costs up to a seventh of the step where the other form is
+    // ahead at the batch's tile count, and gains as much elsewhere (us a step of the batch,
+    // other form / this one: 32 of 64^3 FP32 175 / 192, 8 of 128x16x128 FP32 59 / 64, 32 of 24^3
+    // FP64 39 / 45; 8 of 64x128x64 FP32 107 / 95, 32 of 32^3 FP64 59 / 48).
     static constexpr int max_tiles = N < 8 || N > 256 || C::lds_bytes > 160 * 1024 ? -1
                                      : sizeof(T) == 4                               ? 640
                                      : N >= 64                                      ? 0

@@ -1,6 +1,6 @@
 // small_plane.h -- the y and z work of one step for grids whose (y, z) plane of all six
-// components fits in LDS and that the (x, z) plane pass does not take (Nx < 16 or Nz < 8,
-// and planes of that pass too large): one workgroup per packed x column.
+// components fits in LDS and that the (x, z) plane pass does not take (Nx < 16 or Nz < 8, and
+// few y beside large or very small planes): one workgroup per packed x column.
 //
 // After the x pass, a column kx of the packed half spectrum holds, for each component,
 // the Ny x Nz plane of coefficients (kx, y, z).  The forward transforms along z and y,

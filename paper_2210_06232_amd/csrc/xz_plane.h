@@ -31,8 +31,11 @@ struct XzCfg {
     // Rows of the plane in LDS have one empty element after every 16 and a pitch of 4 mod 16
     // elements: the stores of a radix-16 stage and the reads of four adjacent rows or
     // columns then fall in different banks (128^3 step 105.5 us FP64, 68.3 FP32 against
-    // 109.7 and 71.2 with plain rows of odd pitch).  Planes that fit only without the gaps
-    // (192 x 192 in FP32) keep plain rows.
+    // 109.7 and 71.2 with plain rows of odd pitch).  Planes that fit a CU only without the gaps
+    // (FP64 96 x 96 and 16 x 512, for example) keep plain rows.  In FP32, where XzPair takes
+    // planes of half a CU, the gaps shut six pairs out that would fit with plain rows (M x Nz 8,
+    // 12 and 16 x 512, 48 x 192, 96 x 96, 192 x 48): those run the separate passes, and plain
+    // rows have not been timed for them.
     static constexpr int padded() {
         int q = M - 1 + ((M - 1) >> 4) + 1;
         while (q % 16 != 4) ++q;

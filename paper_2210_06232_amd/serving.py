@@ -178,7 +178,8 @@ def run_stream(n_requests=64, load=0.8, pool=1, budget=24 * 10 ** 9, max_batch=3
            "rate_per_s": None if burst else rate, "mean_service_s": mean_service, "pool": pool,
            "max_steps": max_steps, "budget_bytes": budget, "max_batch": max_batch,
            "step_ms": {f"{s[0]}x{s[1]}x{s[2]}_{p}": round(v * 1e3, 4) for (s, p), v in sorted(step_s.items())}}
-    # mode: (max batch, server flags, forced precision, request flags)
+    # mode: (max batch, server flags, forced precision, request flags).  batched_no_graphs is
+    # batched under another label since the server captures no graphs
     settings = {"batched": (max_batch, 0, None, 0),
                 "batched_no_graphs": (max_batch, eifp.EIFP_SERVER_NO_GRAPHS, None, 0),
                 "serial_own": (1, eifp.EIFP_SERVER_SERIAL, None, 0),
