@@ -198,6 +198,30 @@ template <bool INV, typename T> struct Dft<6, INV, T> {
 template <bool INV, typename T> struct Dft<8, INV, T> {
     __device__ __forceinline__ static void run(cpx<T>* a) { dft_split<4, 2, INV, T>(a); }
 };
+// Dft<8> in FP64 with sqrt(1/2) in two parts (see Comp8).  (x + i y)(1 -+ i) is formed first,
+// so that the second part costs one operation a component.
+constexpr double kSqrtHalfLo = -4.833646656726457e-17;  // sqrt(1/2) minus its double, kCos48q[6]
+template <bool INV>
+__device__ __forceinline__ void dft8_comp(cpx<double>* a) {
+    auto mul = [](double p) { return __builtin_fma(p, kCos48q[6], p * kSqrtHalfLo); };
+    cpx<double> y[2][4];
+#pragma unroll
+    for (int n2 = 0; n2 < 2; ++n2) {
+#pragma unroll
+        for (int n1 = 0; n1 < 4; ++n1) y[n2][n1] = a[2 * n1 + n2];
+        Dft<4, INV, double>::run(y[n2]);
+    }
+    const cpx<double> u = y[1][1], w = y[1][3];
+    // exp(-+i pi/4) and exp(-+3 i pi/4)
+    y[1][1] = INV ? cpx<double>{mul(u.x - u.y), mul(u.x + u.y)} : cpx<double>{mul(u.x + u.y), mul(u.y - u.x)};
+    y[1][2] = twc<8, INV>(2, y[1][2]);
+    y[1][3] = INV ? cpx<double>{mul(-w.x - w.y), mul(w.x - w.y)} : cpx<double>{mul(w.y - w.x), mul(-w.x - w.y)};
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) {
+        a[k1] = y[0][k1] + y[1][k1];
+        a[k1 + 4] = y[0][k1] - y[1][k1];
+    }
+}
 template <bool INV, typename T> struct Dft<12, INV, T> {
     __device__ __forceinline__ static void run(cpx<T>* a) { dft_split<4, 3, INV, T>(a); }
 };
@@ -212,6 +236,18 @@ template <int N_, int E_, int... Rs>
 struct PlanDef {
     static constexpr int N = N_, E = E_, T = N_ / E_, S = sizeof...(Rs);
     static constexpr int R[S] = {Rs...};
+    static constexpr bool COMP8 = false;
+};
+// The same plan, its radix-8 butterflies with sqrt(1/2) in two parts in FP64 (FP32 products
+// always are).  The double of sqrt(1/2) is 6.8e-17 too large relatively, so every value that
+// meets it gains energy: with the plain constant a transform gains 6.6e-17 by the plan (8, 8)
+// and 3.4e-17 by (8, 4), against 2.8e-17 by (16, 4) and 2.2e-17 by (16, 2), whose constants' errors
+// partly cancel, and a run's error grows with it (64x32x64 FP64, 40 steps against the exact
+// flow in 64 bits: (16, 4) 6.2e-15, (8, 8) 8.8e-15, (8, 8) in two parts 5.5e-15, at the same
+// 19.5 us a step).
+template <class P>
+struct Comp8 : P {
+    static constexpr bool COMP8 = true;
 };
 
 template <int N, int E> struct Plan;
@@ -244,8 +280,7 @@ EIFP_PLAN(256, 8, 8, 8, 4)
 EIFP_PLAN(384, 12, 12, 4, 4, 2)
 EIFP_PLAN(512, 16, 16, 16, 2)
 EIFP_PLAN(512, 8, 8, 8, 8)
-// fewer values per thread: 32 and 64 at four (with 16 above) for small FP64 planes of the (x, z)
-// plane pass, the rest for tuning builds of the fused pass
+// fewer values per thread (low register pressure), for tuning builds of the fused pass
 EIFP_PLAN(8, 4, 4, 2)
 EIFP_PLAN(32, 4, 4, 4, 2)
 EIFP_PLAN(64, 4, 4, 4, 4)
@@ -302,7 +337,8 @@ __device__ __forceinline__ void fft_stages(cpx<T> (&v)[P::E], int t, Lds& lds, c
                     v[u * R + r] = twmul<INV, ((CT >> s) & 1) != 0>(tw, (jm * r * (N / (NS * R))) * TWS, N * TWS, v[u * R + r]);
             }
         }
-        Dft<R, INV, T>::run(&v[u * R]);
+        if constexpr (P::COMP8 && R == 8 && sizeof(T) == 8) dft8_comp<INV>(&v[u * R]);
+        else Dft<R, INV, T>::run(&v[u * R]);
     }
     if constexpr (s + 1 < P::S) {
         constexpr int R2 = P::R[s + 1];

@@ -1,6 +1,8 @@
 // passes_impl.h -- plan and tile selection per axis length, and the launchers.
 // Included once per precision (passes_f64.hip, passes_f32.hip).
 #pragma once
+#include <type_traits>
+
 #include "passes.h"
 #include "small_plane.h"
 #include "xz_plane.h"
@@ -484,27 +486,22 @@ int launch_plane(const Grid3& g, const void* md, int nm, const void* twy, const 
 // separate passes / plane pass, Ny = 64: 192x64x64 FP32 68.0 / 52.8, 128x64x192 84.5 /
 // 86.7, 64x64x512 109 / 121; FP64 192x64x96 131 / 115, 128x64x128 99 / 71).
 // Values per thread of the plane pass: as the separate passes on large planes (fewest
-// stages), fewer on small ones, where twice or four times the waves, each with a half or a
-// quarter of the serial work, count for more.  FP32: 8 at lengths 32 and 64, 4 at 16, on
-// planes up to 2048 points (us per step, 16 values / 8: 64^3 22.2 / 20.2; but 128x64x64 33.9
-// / 34.5).  FP64: 4 up to 1024 points, and at length 16 up to 4096 (16 values / 4: 32^3 14.0 /
-// 12.8, 64x32x32 17.1 / 15.7, 32x64x64 20.6 / 19.9; but 64^3, 2048 points, 30.5 / 30.6, 64x128x64
-// 34.9 / 37.8).  Not 8 in FP64, which is as fast or faster (64^3 28.4): its plans (8, 8) and (8,
-// 4) take more values through the rounded sqrt(2)/2, 6.8e-17 too large relatively, so that
-// every transform gains more energy than with (16, 4), (16, 2) or fours and the error of a run
-// grows faster (64^3, 40 steps, against the exact flow in 64 bits: 8 values 8.0e-15, 16 values
-// 5.8e-15, 4 values 5.5e-15; FP32 products are compensated).
+// stages); 8, or 4 at length 16, on small ones, where twice or four times the waves, each
+// with a half or a quarter of the serial work, count for more (us per step, 16 values / 8:
+// 64^3 FP64 30.5 / 28.4, 32^3 FP64 14.0 / 12.9, 64^3 FP32 22.2 / 20.2, 64x64x128 FP64 39.3 /
+// 38.0; but 128x64x64 FP32 33.9 / 34.5 and 128^3 FP64 95 / 150).  In FP64 the plans with 8
+// values, (8, 8) and (8, 4), take sqrt(1/2) in two parts (Comp8).
 template <typename T, int N, int PLANE> struct XZE {
-    static constexpr int E32 = PLANE > 2048 ? XYE<N>::E : N == 16 ? 4 : N == 32 || N == 64 ? 8 : XYE<N>::E;
-    static constexpr int E64 = (N == 16 && PLANE <= 4096) || ((N == 32 || N == 64) && PLANE <= 1024) ? 4 : XYE<N>::E;
-    static constexpr int E = sizeof(T) == 8 ? E64 : E32;
+    static constexpr bool small = PLANE <= (sizeof(T) == 8 ? 4096 : 2048);
+    static constexpr int E = !small ? XYE<N>::E : N == 16 ? 4 : N == 32 || N == 64 ? 8 : XYE<N>::E;
+    using P = std::conditional_t<sizeof(T) == 8 && E == 8 && N != 8, Comp8<Plan<N, E>>, Plan<N, E>>;
 };
 template <typename T, int M, int N> struct XzPair {
     static constexpr bool ok() {
         if constexpr (M < 8 || N < 8 || M * N > 10240) {
             return false;
         } else {
-            using C = XzCfg<T, Plan<N, XZE<T, N, M * N>::E>, Plan<M, XZE<T, M, M * N>::E>>;
+            using C = XzCfg<T, typename XZE<T, N, M * N>::P, typename XZE<T, M, M * N>::P>;
             return C::lds_bytes <= (sizeof(T) == 4 ? C::HALF : C::FULL);
         }
     }
@@ -512,8 +509,8 @@ template <typename T, int M, int N> struct XzPair {
 template <typename T, int M, int N>
 int run_xz(int kind, const Grid3& g, const void* md, int nm, const void* twx, const void* twz, hipStream_t st,
            int fin_nparts) {
-    using PZ = Plan<N, XZE<T, N, M * N>::E>;
-    using PX = Plan<M, XZE<T, M, M * N>::E>;
+    using PZ = typename XZE<T, N, M * N>::P;
+    using PX = typename XZE<T, M, M * N>::P;
     using C = XzCfg<T, PZ, PX>;
     const int nplanes = 6 * g.ny;
     int nwg = nplanes;

@@ -1,12 +1,14 @@
-"""The energy that FP64 steps gain from the transforms' rounded constants, on planes whose
-lengths 32 and 64 can be transformed in several ways: the plans differ in how many values
-meet sqrt(2)/2, whose rounded value is 6.8e-17 too large relatively.
+"""The energy that FP64 steps gain from the transforms' rounded constants, on (x, z) planes
+with the plans (8, 8) and (8, 4), whose radix-8 butterflies take sqrt(1/2) in two parts (its
+double is 6.8e-17 too large relatively), and the same bits from those plans over call
+patterns.
 
 Gates, relative energy a step over 400 steps, halfway between what the separate passes'
-plans give on these fields (2.3e-16, 2.1e-16, 1.7e-16, 1.0e-16) and what (8, 8) and (8, 4) gave
-(3.4e-16, 2.6e-16, 2.9e-16, 2.2e-16)."""
+plans give on these fields (2.3e-16, 2.1e-16, 1.7e-16, 1.0e-16) and what (8, 8) and (8, 4) give
+with the plain constant (3.4e-16, 2.6e-16, 2.9e-16, 2.2e-16)."""
 import math
 
+import numpy as np
 import pytest
 
 from paper_2210_06232_amd import inputs
@@ -28,3 +30,19 @@ def test_energy_gain_per_step(shape, gate):
         gain = (s.invariants()["energy"] / before - 1.0) / n
     print(f"{shape}: {gain:.3e} a step")
     assert abs(gain) <= gate
+
+
+@pytest.mark.parametrize("shape", [(64, 12, 64), (32, 16, 32), (64, 8, 128)], ids=lambda s: "x".join(map(str, s)))
+def test_call_patterns_give_the_same_bits(shape):
+    from paper_2210_06232_amd import eifp as m
+    H, E = inputs.random_fields(shape, CUBE, workload=72, p=2.0)
+    out = []
+    for calls in ((5,), (1,) * 5, (2, 3)):
+        with m.Solver(H, E, CUBE, 1.1, 0.9, "fp64") as s:
+            for n in calls:
+                s.step(0.13, n)
+            out.append((*s.fields(), s.invariants()))
+    for Hg, Eg, inv in out[1:]:
+        np.testing.assert_array_equal(Hg, out[0][0])
+        np.testing.assert_array_equal(Eg, out[0][1])
+        assert inv["energy"] == out[0][2]["energy"] and inv["helicity"] == out[0][2]["helicity"]
