@@ -694,9 +694,11 @@ eifp_status validate_request(const eifp_request* rq) {
 namespace {
 
 constexpr long long kStageHalf = 16LL << 20;  // bytes
-// Arrays from this size on go through staging memory; below, the copy itself is the shorter
-// part (FP64 64^3, 6 MB an array: 0.82 ms directly, 0.98 staged; FP32 64^3, 3 MB: 3.3 / 0.91).
-constexpr long long kStageFrom64 = 8LL << 20, kStageFrom32 = 1LL << 20;
+// Arrays from this size on go through staging memory; FP64 ones below the larger size only
+// if the destination's pages are still to be faulted in, which the copying threads share
+// (64^3 FP64, 6 MB an array: into fresh memory 2.7 ms directly, 1.0 staged; into memory in
+// use 0.77 and 0.98.  FP32 64^3: 3.3 and 0.91).
+constexpr long long kStageFrom = 1LL << 20, kStageFrom64 = 8LL << 20;
 
 void* stage_alloc() {
     void* p = nullptr;
@@ -734,7 +736,10 @@ hipError_t copy_staged(char* stage, const T* from, double* to, long long n, hipS
 template <typename T>
 hipError_t copy_out(eifp_server* sv, const T* from, double* H, double* E, long long n3, hipStream_t io) {
     hipError_t e;
-    const bool large = n3 * (long long)sizeof(T) >= (sizeof(T) == 8 ? kStageFrom64 : kStageFrom32);
+    const long long bytes = n3 * (long long)sizeof(T);
+    const bool large = bytes >= kStageFrom && (sizeof(T) == 4 || bytes >= kStageFrom64 ||
+                                               !looks_resident((const char*)H, n3 * 8) ||
+                                               !looks_resident((const char*)E, n3 * 8));
     if (char* stage = large ? (char*)sv->stages.take(stage_alloc) : nullptr) {
         e = copy_staged<T>(stage, from, H, n3, io);
         if (e == hipSuccess) e = copy_staged<T>(stage, from + n3, E, n3, io);
